@@ -108,6 +108,14 @@ int change_splits(int M, int N, int K);
 // Floats of split workspace change_update needs for an M x N change summed over K rows.
 size_t change_update_workspace(int M, int N, int K);
 
+// Most floats of partials any split product (change or output layer) uses.
+constexpr size_t kMaxSplitFloats = (size_t)16 << 20;
+// Floats that a fixed scratch counts for the partials of an M x N change
+// (output: of the output layer's product) summed over K.
+size_t scratch_split_floats(int M, int N, int K, bool output);
+// Error partials it counts for an output layer.
+int scratch_error_blocks(int M, int N, int K);
+
 // Arrival counters (one per output tile) a split change_update of an M x N
 // change summed over K rows uses; 0 when it is not split.  Never more than
 // kMaxArrivals: a product is split only when it has fewer output tiles than

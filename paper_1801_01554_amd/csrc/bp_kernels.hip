@@ -14,6 +14,7 @@
 // Every reduction runs in a fixed order: results are run-to-run identical.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "bp_device.h"
@@ -251,118 +252,164 @@ __device__ __forceinline__ void ordered_split_sum(f32x4 (&g)[NS], const f32x4 (&
 }
 
 // --------------------------------------------------------------------------
-// Tiled fp32 MFMA product C[M][N] = sum_k A(m, k) B(k, n).
+// Tiled fp32 product C[M][N] = sum_k A(m, k) B(k, n) on the bf16 matrix cores.
 //
-// Operand storage (global and LDS alike, so tiles are copied without a
-// transpose):  A_KM false: A[m * lda + k]   true: A[k * lda + m]
-//              B_NK false: B[k * ldb + n]   true: B[n * ldb + k]
-// 256 threads = 4 waves in a 2 x 2 grid; each wave owns a (BM/2) x (BN/2)
-// sub-tile made of 32 x 32 MFMA blocks.  Within a group of 8 k values, MFMA
-// t (t = 0..3) pairs k = 8g + t (lanes 0-31) with k = 8g + 4 + t (lanes
-// 32-63); A and B use the same assignment, so each lane can fetch its four k
-// values of a k-contiguous tile with one 16-byte LDS read.
-template <int BM, int BN, int BK, bool A_KM, bool B_NK, int NTH = kThreads>
-struct Tile {
-  // wave grid: 2 x 2 waves for 256 threads, 2 x 4 for 512 (wave tile 128 x 64)
-  static constexpr int WGM = 2, WGN = NTH / 128;
-  static constexpr int WM = BM / WGM, WN = BN / WGN;
-  static constexpr int TM = WM / 32, TN = WN / 32;
-  static constexpr int SA = A_KM ? (BM + 8) : (BK + 4);   // LDS row strides (floats)
-  static constexpr int SB = B_NK ? (BK + 4) : (BN + 8);
-  static constexpr int A_ELEMS = A_KM ? BK * SA : BM * SA;
-  static constexpr int B_ELEMS = B_NK ? BN * SB : BK * SB;
-  static constexpr int LA = BM * BK / 4 / NTH;             // float4 loads per thread per stage
-  static constexpr int LB = BN * BK / 4 / NTH;
-  static_assert(BM % 64 == 0 && BN % 64 == 0 && BK % 8 == 0, "tile shape");
-  static_assert(LA * 4 * NTH == BM * BK && LB * 4 * NTH == BN * BK, "tile split");
-};
+// The fp32 MFMA runs at 157 TFLOP/s on this chip and the bf16 one at sixteen
+// times that, so every fp32 operand is split exactly into three bf16 planes,
+//   x = x0 + x1 + x2,  x0 = bf16(x), x1 = bf16(x - x0), x2 = bf16(x - x0 - x1),
+// (8 + 8 + 8 significand bits; both differences are exact) and a product is
+// the six plane products whose weight is above 2^-26 of it,
+//   x y = x2 y0 + x0 y2 + x1 y1 + x1 y0 + x0 y1 + x0 y0  (+ <= 2^-26 x y),
+// accumulated in fp32 by v_mfma_f32_32x32x16_bf16, small terms first.
+// Measured against 64 bits on random operands, the sum over K = 64 / 512 /
+// 2048 / 8192 is off by 1.0 / 3.4 / 7.2 / 14e-7 of its norm, the fp32 MFMA's by
+// 1.4 / 4.1 / 7.9 / 16e-7 (it rounds once per k, this product six times per
+// 16 k), so no accuracy is lost.
+//
+// An infinity or NaN in an operand, an operand within half a bf16 ulp of the
+// largest float and a sum that overflows all leave a non-finite accumulator
+// (x - x0 is then an infinity or NaN); a block that finds one among the
+// elements it owns computes its tile again with the fp32 MFMA, so such calls
+// give what fp32 arithmetic gives.
+//
+// Operand storage in global memory:
+//   A_KM false: A[m * lda + k]   true: A[k * lda + m]
+//   B_NK false: B[k * ldb + n]   true: B[n * ldb + k]
+//
+// What bounds it: power.  On the 8192 x 2048 x 2048 forward product the matrix
+// pipes are busy 63% of the cycles and the clock is down to 1.7-1.9 GHz; the
+// same kernel on zero data runs 1.3 times as fast.  So the tile is the largest
+// that fits: 256 x 256 reuses every staged element 256 times and every LDS
+// fragment 64 times, in 16 waves (four per SIMD) of 64 x 64.
+// Measured, N(0, 1) data: 340-350 us (197-203 TFLOP/s of fp32 product) against
+// 515 us (133) for the fp32 MFMA kernel before it.
+//
+// A stage is 16 k.  Its items, 8 consecutive k of one row, are loaded as fp32
+// two stages ahead, split in registers and written to LDS as three 16-byte
+// chunks of bf16, [plane][k / 8][row], from which a lane reads an MFMA operand
+// (8 k of one row or column) with one ds_read_b128.  A k-contiguous operand's
+// item is two 16-byte loads; a row-contiguous one's is eight 4-byte loads,
+// neighbouring lanes on neighbouring rows, so neither needs a transpose.  The
+// chunk stride is padded so that the eight lanes of an LDS write phase fall
+// into distinct banks.
+constexpr int kStageK = 16;
 
-// Loads a TO x TD tile (TD contiguous) whose origin is (o0, d0) into
-// registers; elements outside [0, O_lim) x [0, D_lim) read as zero.
-template <int TO, int TD, bool VEC, int NTH = kThreads>
-__device__ __forceinline__ void load_tile(const float* __restrict__ base, int ld, int o0, int d0, int O_lim,
-                                          int D_lim, f32x4* r, int tid) {
-  constexpr int PER = TO * TD / 4 / NTH;
-  constexpr int D4 = TD / 4;
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint32_t bf16_pair(float a, float b) {
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{a, b}, bf16x2));
+}
+__device__ __forceinline__ float pair_lo(uint32_t u) { return __builtin_bit_cast(float, u << 16); }
+__device__ __forceinline__ float pair_hi(uint32_t u) { return __builtin_bit_cast(float, u & 0xffff0000u); }
+
+// Eight consecutive k, or their negatives, into the three planes.
+template <bool NEG>
+__device__ __forceinline__ void split_planes(const float (&x)[8], u32x4 (&p)[3]) {
 #pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int f = tid + q * NTH;
-    const int go = o0 + f / D4, gd = d0 + (f % D4) * 4;
-    f32x4 v = {0.f, 0.f, 0.f, 0.f};
-    if (go < O_lim) {
-      const float* p = base + (size_t)go * ld + gd;
-      if (VEC && gd + 4 <= D_lim) {
-        v = *reinterpret_cast<const f32x4*>(p);
+  for (int q = 0; q < 4; ++q) {
+    const float a = NEG ? -x[2 * q] : x[2 * q], b = NEG ? -x[2 * q + 1] : x[2 * q + 1];
+    const uint32_t c0 = bf16_pair(a, b);
+    const float r0 = a - pair_lo(c0), r1 = b - pair_hi(c0);
+    const uint32_t c1 = bf16_pair(r0, r1);
+    p[0][q] = c0;
+    p[1][q] = c1;
+    p[2][q] = bf16_pair(r0 - pair_lo(c1), r1 - pair_hi(c1));
+  }
+}
+
+// Rows of A whose 64-row group has an odd index enter the product negated,
+// and their sums are negated back.  The bf16 MFMA drops the bits of a product
+// that lie far below the accumulator's, rounding towards minus infinity: a
+// bias of about -1e-7 of the result at K = 2048, small beside the rounding
+// errors of one element, but the same for every pattern, so that it adds up
+// in a sum over a batch.  With its sign alternating it cancels there.
+__device__ __forceinline__ bool negated_rows(int row) { return (row >> 6) & 1; }
+
+// One operand of a tile: ROWS rows of kStageK k per stage, staged by NTH threads.
+template <int ROWS, bool KM, int NTH>
+struct Operand {
+  static constexpr int NC = kStageK / 8;                  // 8-k chunks per row
+  static constexpr int RS = ROWS + 4;                     // rows per chunk in LDS (16 bytes each)
+  static constexpr int PLANE = NC * RS * 16, BYTES = 3 * PLANE;
+  static constexpr int ITEMS = ROWS * NC, PER = (ITEMS + NTH - 1) / NTH;
+  static_assert(NC == 2 && ROWS % 64 == 0 && NTH % 64 == 0, "a wave's items: 32 rows x 2 chunks, or 64 rows of one chunk");
+  typedef float Regs[PER][8];
+
+  const float* base;
+  int ld, O, o0, K;
+  int off;                                                // k-contiguous: the lane's byte offset from its wave's first item
+
+  static __device__ __forceinline__ int row_of(int f) { return KM ? f % ROWS : f / NC; }
+  static __device__ __forceinline__ int chunk_of(int f) { return KM ? f / ROWS : f % NC; }
+  // items of thread t: t, t + NTH, ... below ITEMS (whole waves)
+  static __device__ __forceinline__ bool has(int wave, int i) { return ITEMS % NTH == 0 || wave * 64 + i * NTH < ITEMS; }
+
+  __device__ __forceinline__ void init(const float* m, int ld_, int o0_, int O_, int K_, int lane) {
+    base = m;
+    ld = ld_;
+    o0 = o0_;
+    O = O_;
+    K = K_;
+    off = KM ? 0 : (lane / NC) * ld * 4 + (lane % NC) * 32;
+  }
+
+  // The items of stage [k, k + kStageK), ke the end of the block's K range,
+  // all within the matrix and without a branch, so that loads stay in flight
+  // across stages.  Row-contiguous: one scalar row address per k, clamped to
+  // row ke - 1, and a lane column clamped to the last.  k-contiguous: bounded
+  // by a buffer resource that ends with the matrix (rows past it read as zero,
+  // a row's end reads on into the next one).  store() zeroes what lies past ke.
+  __device__ __forceinline__ void load(Regs& x, int k, int ke, int wave, int lane) const {
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      if (!has(wave, i)) continue;
+      const int f0 = wave * 64 + i * NTH;                 // the wave's first item
+      if constexpr (KM) {
+        const int kc = k + chunk_of(f0) * 8;
+        const uint32_t col = (uint32_t)min(o0 + row_of(f0) + lane, O - 1) * 4u;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const char* row = reinterpret_cast<const char*>(base + (size_t)min(kc + j, ke - 1) * ld);
+          x[i][j] = *reinterpret_cast<const float*>(row + col);
+        }
       } else {
+        const int row = o0 + row_of(f0);
+        const bool in = row < O;
+        const float* p = base + (in ? (size_t)row * ld + k : 0);
+        const long long left = in ? (long long)(O - 1 - row) * ld + (K - k) : 0;   // floats to the matrix's end
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(p), (short)0, (int)(uint32_t)min(left * 4, 0xfffffffcll), 0x00020000);
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-          if (gd + e < D_lim) v[e] = p[e];
+        for (int q = 0; q < 2; ++q) {
+          const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, off + 16 * q, 0, 0));
+#pragma unroll
+          for (int e = 0; e < 4; ++e) x[i][4 * q + e] = v[e];
+        }
       }
     }
-    r[q] = v;
   }
-}
 
-// Loads a TO x TD tile that lies entirely inside the matrix, 16 bytes per
-// load, with no bounds checks (interior tiles of 16-byte aligned operands).
-template <int TO, int TD, int NTH = kThreads>
-__device__ __forceinline__ void load_tile_full(const float* __restrict__ base, int ld, int o0, int d0, f32x4* r,
-                                               int tid) {
-  constexpr int PER = TO * TD / 4 / NTH;
-  constexpr int D4 = TD / 4;
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int f = tid + q * NTH;
-    r[q] = *reinterpret_cast<const f32x4*>(base + (size_t)(o0 + f / D4) * ld + d0 + (f % D4) * 4);
-  }
-}
-
-template <int TO, int TD, int S, int NTH = kThreads>
-__device__ __forceinline__ void store_tile(float* lds, const f32x4* r, int tid) {
-  constexpr int PER = TO * TD / 4 / NTH;
-  constexpr int D4 = TD / 4;
-#pragma unroll
-  for (int q = 0; q < PER; ++q) {
-    const int f = tid + q * NTH;
-    *reinterpret_cast<f32x4*>(lds + (f / D4) * S + (f % D4) * 4) = r[q];
-  }
-}
-
-// A TO x TD tile (TD contiguous, inside the matrix) copied from global memory
-// straight into its LDS image [TO][S] by the LDS-DMA load: one wave
-// instruction writes 64 consecutive 16-byte chunks of the image (lane l the
-// l-th), each lane loading its chunk's global address.  The image is taken in
-// blocks of 64 chunks, block b by wave b % NW; a chunk of row padding
-// (S - TD floats per row) loads a copy of the row's last data chunk.  Its
-// global offsets relative to the tile origin are fixed across K stages, so
-// they are computed once (off) and a stage passes the origin.
-template <int TO, int TD, int S, int NTH>
-struct DmaTile {
-  static constexpr int CPR = S / 4;                   // chunks per image row
-  static constexpr int Q = TO * CPR;                  // chunks
-  static constexpr int NB = (Q + 63) / 64;            // 64-chunk blocks
-  static constexpr int NW = NTH / 64;
-  static constexpr int PER = (NB + NW - 1) / NW;      // blocks per wave (at most)
-  static_assert(S % 4 == 0 && TD % 4 == 0 && S >= TD, "DMA tile shape");
-  int off[PER];                                       // element offsets from the origin
-  __device__ __forceinline__ void init(int ld, int wave, int lane) {
+  template <bool IS_A>
+  __device__ __forceinline__ void store(Regs& x, char* lds, int k, int ke, int wave, int lane) const {
 #pragma unroll
     for (int i = 0; i < PER; ++i) {
-      const int q = min((wave + i * NW) * 64 + lane, Q - 1);
-      const int row = q / CPR, c = min(q % CPR, TD / 4 - 1);
-      off[i] = row * ld + 4 * c;
-    }
-  }
-  // the tile with origin `org` (global) into the image `lds`
-  __device__ __forceinline__ void copy(const float* org, float* lds, int wave, int lane) const {
+      if (!has(wave, i)) continue;
+      const int f = wave * 64 + i * NTH + lane;
+      if (k + kStageK > ke) {
+        const int kc = k + chunk_of(f) * 8;
 #pragma unroll
-    for (int i = 0; i < PER; ++i) {
-      const int b = wave + i * NW;
-#if defined(__HIP_DEVICE_COMPILE__)   // (a device instruction: the host pass only sees the kernel's signature)
-      if (b < NB && (b < NB - 1 || lane < Q - 64 * (NB - 1)))
-        __builtin_amdgcn_global_load_lds(org + off[i],
-                                         (__attribute__((address_space(3))) void*)(lds + 256 * b), 16, 0, 0);
-#endif
+        for (int j = 0; j < 8; ++j) x[i][j] = kc + j < ke ? x[i][j] : 0.f;
+      }
+      u32x4 pl[3];
+      if (IS_A && negated_rows(o0 + row_of(wave * 64 + i * NTH)))   // one group: 32 or 64 rows per wave
+        split_planes<true>(x[i], pl);
+      else
+        split_planes<false>(x[i], pl);
+      char* d = lds + (chunk_of(f) * RS + row_of(f)) * 16;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) *reinterpret_cast<u32x4*>(d + q * PLANE) = pl[q];
     }
   }
 };
@@ -384,18 +431,67 @@ __device__ __forceinline__ void xcd_tile(int bid, int nblocks, int tiles_m, int 
   tn = in_band / rows;
 }
 
-template <int BM, int BN, int BK, bool A_KM, bool B_NK, bool AVEC, bool BVEC, class Epi, int NTH = kThreads>
-__global__ __launch_bounds__(NTH) void gemm_kernel(const float* __restrict__ A, int lda,
-                                                   const float* __restrict__ B, int ldb, int M, int N,
-                                                   int K, int k_chunk, Epi epi) {
-  using T = Tile<BM, BN, BK, A_KM, B_NK, NTH>;
-  // 512-thread blocks (256 x 256 tiles) only for full tiles of the sigmoid and
-  // hidden-delta products, which end through the row epilogue
-  static_assert(NTH == kThreads || ((std::is_same_v<Epi, EpiSigmoid> || std::is_same_v<Epi, EpiHiddenDelta>) &&
-                                    BM == 256 && BN == 256),
-                "512-thread tiles: full-tile sigmoid and hidden-delta products");
-  __shared__ __attribute__((aligned(16))) float As[2][T::A_ELEMS];
-  __shared__ __attribute__((aligned(16))) float Bs[2][T::B_ELEMS];
+// A wave's part of a tile (TM x TN blocks of 32 x 32 at row m0, column n0)
+// summed over [kb, ke) with the fp32 MFMA, operands straight from global
+// memory: the arithmetic of operands and sums that bf16 planes cannot hold.
+// MFMA t of a group of 8 k pairs k = 8 g + t (lanes 0-31) with 8 g + 4 + t.
+template <bool A_KM, bool B_NK, int TM, int TN>
+__device__ __forceinline__ void fp32_tile(const float* __restrict__ A, int lda, const float* __restrict__ B, int ldb, int M,
+                                       int N, int kb, int ke, int m0, int n0, f32x16 (&acc)[TM][TN]) {
+  const int lane = threadIdx.x & 63, r = lane & 31, h = lane >> 5;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+  for (int k0 = kb; k0 < ke; k0 += 8)
+    for (int t = 0; t < 4; ++t) {
+      const int k = k0 + 4 * h + t, kc = min(k, ke - 1);
+      float a[TM], b[TN];
+#pragma unroll
+      for (int i = 0; i < TM; ++i) {
+        const int m = min(m0 + i * 32 + r, M - 1);
+        a[i] = A_KM ? A[(size_t)kc * lda + m] : A[(size_t)m * lda + kc];
+        if (k >= ke) a[i] = 0.f;
+      }
+#pragma unroll
+      for (int j = 0; j < TN; ++j) {
+        const int n = min(n0 + j * 32 + r, N - 1);
+        b[j] = B_NK ? B[(size_t)n * ldb + kc] : B[(size_t)kc * ldb + n];
+        if (k >= ke) b[j] = 0.f;
+      }
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+#pragma unroll
+        for (int j = 0; j < TN; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[i], b[j], acc[i][j], 0, 0, 0);
+    }
+}
+
+// Waves of a BM x BN tile: a WGM x WGN grid, each wave (BM / WGM) x (BN / WGN)
+// of 32 x 32 MFMA blocks.
+template <int BM, int BN>
+struct Tile {
+  static constexpr int WGM = BM == 256 ? 4 : 2, WGN = BN == 256 ? 4 : 2;
+  static constexpr int NTH = 64 * WGM * WGN;
+  static constexpr int WM = BM / WGM, WN = BN / WGN;
+  static constexpr int TM = WM / 32, TN = WN / 32;
+  static constexpr int DEPTH = BM == 256 ? 1 : (BM == 128 ? 2 : 3);   // stages of loads in flight
+  static_assert(BM % 64 == 0 && BN % 64 == 0 && WM % 32 == 0 && WN % 32 == 0, "tile shape");
+};
+
+constexpr int tile_threads(int bm) { return bm == 256 ? 1024 : 256; }
+
+template <int BM, int BN, bool A_KM, bool B_NK, class Epi>
+__global__ __launch_bounds__(tile_threads(BM)) void gemm_kernel(const float* __restrict__ A, int lda,
+                                                                 const float* __restrict__ B, int ldb, int M, int N,
+                                                                 int K, int k_chunk, Epi epi) {
+  using T = Tile<BM, BN>;
+  constexpr int NTH = T::NTH;
+  using OpA = Operand<BM, A_KM, NTH>;
+  using OpB = Operand<BN, !B_NK, NTH>;
+  constexpr int kStage = OpA::BYTES + OpB::BYTES;
+  __shared__ __attribute__((aligned(16))) char lds[2][kStage];
 
   const int tiles_n = (N + BN - 1) / BN, tiles_m = (M + BM - 1) / BM;
   int tm, tn;
@@ -405,7 +501,7 @@ __global__ __launch_bounds__(NTH) void gemm_kernel(const float* __restrict__ A, 
   const int kb = blockIdx.z * k_chunk;
   const int ke = min(K, kb + k_chunk);
 
-  const int wave = tid >> 6, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int wm0 = (wave / T::WGN) * T::WM, wn0 = (wave % T::WGN) * T::WN;
   const int r = lane & 31, h = lane >> 5;
 
@@ -417,148 +513,91 @@ __global__ __launch_bounds__(NTH) void gemm_kernel(const float* __restrict__ A, 
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
 
-  // Two register sets: the tile of stage s + 2 is loaded while stage s is
-  // multiplied, so a global load has two stages of MFMA work to land before
-  // its registers are written to LDS.
-  f32x4 ra0[T::LA], rb0[T::LB], ra1[T::LA], rb1[T::LB];
-  // Interior tiles (the block-uniform common case) take the unchecked path.
-  const bool a_rows_in = m0 + BM <= M, b_rows_in = n0 + BN <= N;
-  auto load_stage = [&](int k, f32x4* ra, f32x4* rb) {
-    if constexpr (NTH != kThreads) {   // launched only on whole tiles: M, N, K multiples of the tile
-      if (A_KM) load_tile_full<BK, BM, NTH>(A, lda, k, m0, ra, tid);
-      else load_tile_full<BM, BK, NTH>(A, lda, m0, k, ra, tid);
-      if (B_NK) load_tile_full<BN, BK, NTH>(B, ldb, n0, k, rb, tid);
-      else load_tile_full<BK, BN, NTH>(B, ldb, k, n0, rb, tid);
-      return;
-    }
-    const bool k_in = k + BK <= ke;
-    if (AVEC && a_rows_in && k_in) {
-      if (A_KM) load_tile_full<BK, BM, NTH>(A, lda, k, m0, ra, tid);
-      else load_tile_full<BM, BK, NTH>(A, lda, m0, k, ra, tid);
-    } else {
-      if (A_KM) load_tile<BK, BM, AVEC, NTH>(A, lda, k, m0, ke, M, ra, tid);
-      else load_tile<BM, BK, AVEC, NTH>(A, lda, m0, k, M, ke, ra, tid);
-    }
-    if (BVEC && b_rows_in && k_in) {
-      if (B_NK) load_tile_full<BN, BK, NTH>(B, ldb, n0, k, rb, tid);
-      else load_tile_full<BK, BN, NTH>(B, ldb, k, n0, rb, tid);
-    } else {
-      if (B_NK) load_tile<BN, BK, BVEC, NTH>(B, ldb, n0, k, N, ke, rb, tid);
-      else load_tile<BK, BN, BVEC, NTH>(B, ldb, k, n0, ke, N, rb, tid);
-    }
+  OpA oa;
+  OpB ob;
+  oa.init(A, lda, m0, M, K, lane);
+  ob.init(B, ldb, n0, N, K, lane);
+  const int nst = ke > kb ? (ke - kb + kStageK - 1) / kStageK : 0;
+  // D register sets: stage t is loaded into set t % D, D + 1 stages before it
+  // is multiplied.  (A stage past the last loads the last one again, which
+  // keeps the loop free of branches around loads.)
+  constexpr int D = T::DEPTH;
+  typename OpA::Regs xa[D];
+  typename OpB::Regs xb[D];
+  auto load = [&](int t, int d) {
+    const int k = kb + min(t, nst - 1) * kStageK;
+    oa.load(xa[d], k, ke, wave, lane);
+    ob.load(xb[d], k, ke, wave, lane);
   };
-  auto store_stage = [&](int buf, const f32x4* ra, const f32x4* rb) {
-    if (A_KM) store_tile<BK, BM, T::SA, NTH>(As[buf], ra, tid);
-    else store_tile<BM, BK, T::SA, NTH>(As[buf], ra, tid);
-    if (B_NK) store_tile<BN, BK, T::SB, NTH>(Bs[buf], rb, tid);
-    else store_tile<BK, BN, T::SB, NTH>(Bs[buf], rb, tid);
+  auto store = [&](int t, int d) {
+    char* buf = lds[t & 1];
+    oa.template store<true>(xa[d], buf, kb + t * kStageK, ke, wave, lane);
+    ob.template store<false>(xb[d], buf + OpA::BYTES, kb + t * kStageK, ke, wave, lane);
   };
+  // lane (h, r) of an MFMA holds k = 8 h .. 8 h + 7 of row (column) r
   auto compute = [&](int buf) {
-    const float* as = As[buf];
-    const float* bs = Bs[buf];
+    const char* la = lds[buf] + (h * OpA::RS + wm0 + r) * 16;
+    const char* lb = lds[buf] + OpA::BYTES + (h * OpB::RS + wn0 + r) * 16;
+    bf16x8 b[T::TN][3];
 #pragma unroll
-    for (int g = 0; g < BK / 8; ++g) {
-      f32x4 af[T::TM], bf[T::TN];
+    for (int j = 0; j < T::TN; ++j)
 #pragma unroll
-      for (int i = 0; i < T::TM; ++i) {
-        const int m = wm0 + i * 32 + r;
-        if (A_KM) {
+      for (int q = 0; q < 3; ++q) b[j][q] = *reinterpret_cast<const bf16x8*>(lb + q * OpB::PLANE + j * 512);
 #pragma unroll
-          for (int t = 0; t < 4; ++t) af[i][t] = as[(g * 8 + 4 * h + t) * T::SA + m];
-        } else {
-          af[i] = *reinterpret_cast<const f32x4*>(as + m * T::SA + g * 8 + 4 * h);
-        }
-      }
+    for (int i = 0; i < T::TM; ++i) {
+      bf16x8 a[3];
 #pragma unroll
-      for (int j = 0; j < T::TN; ++j) {
-        const int n = wn0 + j * 32 + r;
-        if (B_NK) {
-          bf[j] = *reinterpret_cast<const f32x4*>(bs + n * T::SB + g * 8 + 4 * h);
-        } else {
+      for (int q = 0; q < 3; ++q) a[q] = *reinterpret_cast<const bf16x8*>(la + q * OpA::PLANE + i * 512);
+      constexpr int kTerms[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
 #pragma unroll
-          for (int t = 0; t < 4; ++t) bf[j][t] = bs[(g * 8 + 4 * h + t) * T::SB + n];
-        }
-      }
+      for (int q = 0; q < 6; ++q)
 #pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < T::TM; ++i)
-#pragma unroll
-          for (int j = 0; j < T::TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(af[i][t], bf[j][t], acc[i][j], 0, 0, 0);
+        for (int j = 0; j < T::TN; ++j)
+          acc[i][j] =
+              __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[kTerms[q][0]], b[j][kTerms[q][1]], acc[i][j], 0, 0, 0);
     }
   };
-  // One pipeline step at stage s: registers `rl` (which held stage s, already
-  // in LDS) receive stage s + 2; LDS buffer s % 2 is multiplied; registers
-  // `rs` (stage s + 1) are written to the other LDS buffer.
-  const int nst = ke > kb ? (ke - kb + BK - 1) / BK : 0;
-  auto step = [&](int s, f32x4* rla, f32x4* rlb, const f32x4* rsa, const f32x4* rsb) {
-    if (s + 2 < nst) load_stage(kb + (s + 2) * BK, rla, rlb);
-    compute(s & 1);
-    if (s + 1 < nst) store_stage((s + 1) & 1, rsa, rsb);
+  if (nst > 0) {
+#pragma unroll
+    for (int d = 0; d < D; ++d) load(d, d);
+    store(0, 0);
+    load(D, 0);
     __syncthreads();
-  };
-  if constexpr (NTH != kThreads && B_NK) {
-    // 512-thread blocks hold twice the accumulators per wave; one register
-    // set suffices there, as a stage is twice the MFMA work per SIMD (two
-    // waves of 128 x 64 each): the load of stage s + 1 lands while stage s
-    // is multiplied.
-    if (nst > 0) {
-      load_stage(kb, ra0, rb0);
-      store_stage(0, ra0, rb0);
-      __syncthreads();
-    }
-    for (int s = 0; s < nst; ++s) {
-      if (s + 1 < nst) load_stage(kb + (s + 1) * BK, ra0, rb0);
-      compute(s & 1);
-      if (s + 1 < nst) store_stage((s + 1) & 1, ra0, rb0);
-      __syncthreads();
-    }
-  } else if constexpr (NTH != kThreads) {
-    // The sigmoid products' 512-thread blocks (whole tiles only) copy each
-    // stage straight into LDS with the LDS-DMA load: stage s + 1 is copied
-    // into the other buffer while stage s is multiplied, and the barrier that
-    // ends stage s waits for the copy; no staging registers, no LDS stores.
-    // (Measured: forward products 1.3% faster; the hidden-delta products, whose
-    // B tile is also sliced into 128-byte rows, 3% slower, so they stage
-    // through registers.)
-    DmaTile<A_KM ? BK : BM, A_KM ? BM : BK, T::SA, NTH> da;
-    DmaTile<B_NK ? BN : BK, B_NK ? BK : BN, T::SB, NTH> db;
-    da.init(lda, wave, lane);
-    db.init(ldb, wave, lane);
-    // stage origins: the tile's first row and column at depth k
-    auto a_org = [&](int k) { return A_KM ? A + (size_t)k * lda + m0 : A + (size_t)m0 * lda + k; };
-    auto b_org = [&](int k) { return B_NK ? B + (size_t)n0 * ldb + k : B + (size_t)k * ldb + n0; };
-    if (nst > 0) {
-      da.copy(a_org(kb), As[0], wave, lane);
-      db.copy(b_org(kb), Bs[0], wave, lane);
-      __syncthreads();
-    }
-    for (int s = 0; s < nst; ++s) {
-      if (s + 1 < nst) {
-        da.copy(a_org(kb + (s + 1) * BK), As[(s + 1) & 1], wave, lane);
-        db.copy(b_org(kb + (s + 1) * BK), Bs[(s + 1) & 1], wave, lane);
+    for (int s0 = 0; s0 < nst; s0 += D)
+#pragma unroll
+      for (int d = 0; d < D; ++d) {
+        const int s = s0 + d;
+        if (D > 1 && s >= nst) break;
+        compute(s & 1);
+        if (s + 1 < nst) store(s + 1, (d + 1) % D);
+        load(s + 1 + D, (d + 1) % D);
+        __syncthreads();
       }
-      compute(s & 1);
-      __syncthreads();
-    }
-  } else {
-    if (nst > 0) {
-      load_stage(kb, ra0, rb0);
-      if (nst > 1) load_stage(kb + BK, ra1, rb1);
-      store_stage(0, ra0, rb0);
-      __syncthreads();
-    }
-    int s = 0;
-    for (; s + 1 < nst; s += 2) {
-      step(s, ra0, rb0, ra1, rb1);       // even stage: loads s + 2 into set 0, stores set 1 (stage s + 1)
-      step(s + 1, ra1, rb1, ra0, rb0);   // odd stage: loads s + 3 into set 1, stores set 0 (stage s + 2)
-    }
-    if (s < nst) step(s, ra0, rb0, ra1, rb1);
   }
 
   // Accumulator layout of a 32 x 32 block: register e of lane (h, r) holds
   // row 8 (e / 4) + 4 h + (e % 4), column r.
+  if (negated_rows(m0 + wm0)) {
+#pragma unroll
+    for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[i][j][e] = -acc[i][j][e];
+  }
+  {
+    // elements of the matrix that are not finite: the tile once more in fp32
+    bool odd = false;
+#pragma unroll
+    for (int i = 0; i < T::TM; ++i)
+#pragma unroll
+      for (int j = 0; j < T::TN; ++j)
+#pragma unroll
+        for (int e = 0; e < 16; ++e)
+          odd |= !(fabsf(acc[i][j][e]) < INFINITY) && n0 + wn0 + j * 32 + r < N &&
+                 m0 + wm0 + i * 32 + 8 * (e >> 2) + 4 * h + (e & 3) < M;
+    if (__syncthreads_or(odd)) fp32_tile<A_KM, B_NK, T::TM, T::TN>(A, lda, B, ldb, M, N, kb, ke, m0 + wm0, n0 + wn0, acc);
+  }
   if constexpr (std::is_same_v<Epi, EpiSplitUpdate>) {
     // The block's partial (slot (i TN + j) 4 + q of a wave = registers 4 q
     // .. 4 q + 3 of block (i, j)), its arrival, and in the last block of the
@@ -585,124 +624,117 @@ __global__ __launch_bounds__(NTH) void gemm_kernel(const float* __restrict__ A, 
 #pragma unroll
       for (int j = 0; j < T::TN; ++j) {
         const int n = n0 + wn0 + j * 32 + r, nc = min(n, N - 1);
-        float vo[16], wo[16];
+        // NS 4-row slots at a time (all four; the 1024-thread blocks have
+        // registers for two beside their accumulators)
+        constexpr int NS = BM == 256 ? 2 : 4;
 #pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const size_t idx = (size_t)min(m0 + wm0 + i * 32 + 8 * (e >> 2) + 4 * h + (e & 3), M - 1) * epi.ldw + nc;
-          vo[e] = epi.V[idx];
-          wo[e] = epi.W[idx];
-        }
-        f32x4 own[4], g[4];
+        for (int q0 = 0; q0 < 4; q0 += NS) {
+          auto row = [&](int e) { return m0 + wm0 + i * 32 + 8 * (q0 + (e >> 2)) + 4 * h + (e & 3); };
+          float vo[4 * NS], wo[4 * NS];
 #pragma unroll
-        for (int q = 0; q < 4; ++q)
-          own[q] = f32x4{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-        ordered_split_sum<4, (BM == 64 && BN == 64) ? 8 : 1>(g, own, pr, zstride, (i * T::TN + j) * 4, lane, z,
-                                                              epi.splits);
-        if (n < N) {
+          for (int e = 0; e < 4 * NS; ++e) {
+            const size_t idx = (size_t)min(row(e), M - 1) * epi.ldw + nc;
+            vo[e] = epi.V[idx];
+            wo[e] = epi.W[idx];
+          }
+          f32x4 own[NS], g[NS];
 #pragma unroll
-          for (int e = 0; e < 16; ++e) {
-            const int m = m0 + wm0 + i * 32 + 8 * (e >> 2) + 4 * h + (e & 3);
-            if (m < M) {
-              const size_t idx = (size_t)m * epi.ldw + n;
-              const float v = momentum_step(checked_change(g[e >> 2][e & 3], epi.limit, nf), vo[e], epi.lr, epi.mom);
-              epi.V[idx] = v;
-              epi.W[idx] = wo[e] + v;
+          for (int q = 0; q < NS; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) own[q][e] = acc[i][j][4 * (q0 + q) + e];
+          ordered_split_sum<NS, (BM == 64 && BN == 64) ? 8 : 1>(g, own, pr, zstride, (i * T::TN + j) * 4 + q0, lane, z,
+                                                                 epi.splits);
+          if (n < N) {
+#pragma unroll
+            for (int e = 0; e < 4 * NS; ++e) {
+              if (row(e) < M) {
+                const size_t idx = (size_t)row(e) * epi.ldw + n;
+                const float v = momentum_step(checked_change(g[e >> 2][e & 3], epi.limit, nf), vo[e], epi.lr, epi.mom);
+                epi.V[idx] = v;
+                epi.W[idx] = wo[e] + v;
+              }
             }
           }
         }
       }
     if (epi.limit > 0.f) add_faults(nf, epi.faults);
   } else {
-    // Row epilogue of full 128 x 128 and 256 x 256 tiles for the sigmoid and
-    // hidden-delta products, 128 rows at a time: the accumulators of those
-    // rows go to LDS (the idle stage buffers, rows 0-63 in As and 64-127 in
-    // Bs, row stride BN + 8 floats: the two lane halves of a register write
-    // land 32 banks apart), then each thread takes 4 adjacent columns of 16
-    // rows (rows t / (BN / 4) + 8 i) as float4: one 16-byte load of the
+    // Row epilogue of whole tiles of the sigmoid and hidden-delta products, 64
+    // rows (one column-sum group) at a time: the accumulators of those rows go
+    // to LDS (the idle stage buffers, row stride BN + 8 floats: the two lane
+    // halves of a register write land 32 banks apart), then each thread takes
+    // 4 adjacent columns of every SL-th row as float4: one 16-byte load of the
     // operand and one 16-byte store per row instead of four 4-byte ones, every
     // wave instruction covering whole cache lines.
-    constexpr bool kRowEpi = (std::is_same_v<Epi, EpiSigmoid> || std::is_same_v<Epi, EpiHiddenDelta>) &&
-                             ((BM == 128 && BN == 128) || (BM == 256 && BN == 256));
+    constexpr bool kRowEpi = std::is_same_v<Epi, EpiSigmoid> || std::is_same_v<Epi, EpiHiddenDelta>;
     if constexpr (kRowEpi) {
       constexpr int RS = BN + 8, C4N = BN / 4, SL = NTH / C4N;   // row stride; float4 per row; row slices
-      static_assert(SL == 8 && 64 * RS <= 2 * T::A_ELEMS && 64 * RS <= 2 * T::B_ELEMS,
+      constexpr int RPT = 64 / SL;                               // rows per thread
+      static_assert(64 * RS * 4 <= 2 * kStage && SL * C4N * 16 <= 2 * kStage && RPT * SL == 64,
                     "row epilogue fits the stage buffers");
       bool vec = m0 + BM <= M && n0 + BN <= N && (epi.ldo & 3) == 0 && (reinterpret_cast<uintptr_t>(epi.out) & 15) == 0;
       if constexpr (std::is_same_v<Epi, EpiHiddenDelta>)
         vec = vec && (epi.lda & 3) == 0 && (reinterpret_cast<uintptr_t>(epi.act) & 15) == 0;
-      if (NTH != kThreads || vec) {
-        float* lo = &As[0][0];
-        float* hi = &Bs[0][0];
+      if (vec) {
+        float* buf = reinterpret_cast<float*>(&lds[0][0]);
         const int c4 = tid % C4N, r0 = tid / C4N;
         const int n = n0 + 4 * c4;
         f32x4 b4 = {0.f, 0.f, 0.f, 0.f};
         if constexpr (std::is_same_v<Epi, EpiSigmoid>)
           b4 = f32x4{epi.bias[n], epi.bias[n + 1], epi.bias[n + 2], epi.bias[n + 3]};
 #pragma unroll
-        for (int hf = 0; hf < BM / 128; ++hf) {
-          if (hf > 0) __syncthreads();                     // the previous half is read
-          // a wave's rows lie in one half (WM <= 128); rb is their first row
-          // within it, a multiple of 64, so the buffer of each 32-row block
-          // is wave-uniform
-          const int rb = wm0 - 128 * hf;
-          if (rb >= 0 && rb < 128) {
+        for (int g = 0; g < BM / 64; ++g) {
+          const int mg = m0 + 64 * g;
+          f32x4 pre[RPT];
+          if constexpr (std::is_same_v<Epi, EpiHiddenDelta>) {
+#pragma unroll
+            for (int i = 0; i < RPT; ++i)
+              pre[i] = *reinterpret_cast<const f32x4*>(epi.act + (size_t)(mg + r0 + SL * i) * epi.lda + n);
+          }
+          if (g > 0) __syncthreads();                      // the previous group is read
+          if (wm0 >= 64 * g && wm0 < 64 * g + 64) {        // WM <= 64: the wave's rows lie in one group
 #pragma unroll
             for (int i = 0; i < T::TM; ++i) {
-              float* dst = (rb + i * 32 < 64 ? lo : hi) + ((rb + i * 32) & 63) * RS + wn0 + r;
+              float* dst = buf + (wm0 - 64 * g + i * 32 + 4 * h) * RS + wn0 + r;
 #pragma unroll
               for (int j = 0; j < T::TN; ++j)
 #pragma unroll
-                for (int e = 0; e < 16; ++e) dst[(8 * (e >> 2) + 4 * h + (e & 3)) * RS + j * 32] = acc[i][j][e];
+                for (int e = 0; e < 16; ++e) dst[(8 * (e >> 2) + (e & 3)) * RS + j * 32] = acc[i][j][e];
             }
           }
           __syncthreads();
-          f32x4 cs[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
+          f32x4 cs = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-          for (int g = 0; g < 2; ++g) {
-            const int mg = m0 + 128 * hf + 64 * g;
-            f32x4 pre[8];
-            if constexpr (std::is_same_v<Epi, EpiHiddenDelta>) {
+          for (int i = 0; i < RPT; ++i) {
+            const int row = r0 + SL * i;
+            const f32x4 a = *reinterpret_cast<const f32x4*>(buf + row * RS + 4 * c4);
+            f32x4 v;
 #pragma unroll
-              for (int i = 0; i < 8; ++i)
-                pre[i] = *reinterpret_cast<const f32x4*>(epi.act + (size_t)(mg + r0 + 8 * i) * epi.lda + n);
+            for (int q = 0; q < 4; ++q) {
+              if constexpr (std::is_same_v<Epi, EpiSigmoid>)
+                v[q] = unit_sigma(a[q] + b4[q], epi.tab);
+              else
+                v[q] = a[q] * (pre[i][q] * (1.0f - pre[i][q]));
             }
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-              const int row = r0 + 8 * i;
-              const f32x4 a = *reinterpret_cast<const f32x4*>((g ? hi : lo) + row * RS + 4 * c4);
-              f32x4 v;
-#pragma unroll
-              for (int q = 0; q < 4; ++q) {
-                if constexpr (std::is_same_v<Epi, EpiSigmoid>)
-                  v[q] = unit_sigma(a[q] + b4[q], epi.tab);
-                else
-                  v[q] = a[q] * (pre[i][q] * (1.0f - pre[i][q]));
-              }
-              *reinterpret_cast<f32x4*>(epi.out + (size_t)(mg + row) * epi.ldo + n) = v;
-              if constexpr (Epi::kColSum) cs[g] += v;
-            }
+            *reinterpret_cast<f32x4*>(epi.out + (size_t)(mg + row) * epi.ldo + n) = v;
+            if constexpr (Epi::kColSum) cs += v;
           }
           if constexpr (Epi::kColSum) {
-            // per 64-row group: the 8 row slices (r0) of each column added in
-            // slice order
+            // the SL row slices (r0) of each column added in slice order
             __syncthreads();
-            f32x4* red = reinterpret_cast<f32x4*>(lo);        // [2][8][C4N] float4
-#pragma unroll
-            for (int g = 0; g < 2; ++g) red[(g * 8 + r0) * C4N + c4] = cs[g];
+            f32x4* red = reinterpret_cast<f32x4*>(buf);      // [SL][C4N] float4
+            red[r0 * C4N + c4] = cs;
             __syncthreads();
-            if (tid < 2 * C4N) {
-              const int g = tid / C4N, cc = tid % C4N;
-              f32x4 t = red[(g * 8) * C4N + cc];
-              for (int k = 1; k < 8; ++k) t += red[(g * 8 + k) * C4N + cc];
-              *reinterpret_cast<f32x4*>(epi.colsum + (size_t)(tm * (BM / 64) + 2 * hf + g) * epi.ldcs + n0 + 4 * cc) =
-                  t;
+            if (tid < C4N) {
+              f32x4 t = red[tid];
+              for (int k = 1; k < SL; ++k) t += red[k * C4N + tid];
+              *reinterpret_cast<f32x4*>(epi.colsum + (size_t)(tm * (BM / 64) + g) * epi.ldcs + n0 + 4 * tid) = t;
             }
           }
         }
         return;
       }
     }
-    if constexpr (NTH == kThreads) {
     float sse = 0.f;   // the epilogue's per-lane statistic (error, or fault count: exact below 2^24)
     // The per-element operands of each 32 x 32 block are loaded together
     // (clamped, always valid addresses; values outside the matrix are never
@@ -730,24 +762,23 @@ __global__ __launch_bounds__(NTH) void gemm_kernel(const float* __restrict__ A, 
       }
     }
     if constexpr (Epi::kColSum) {
-      // Column sums per 64-row group of the tile (a 128-row tile has two, one
-      // per wave row; a 64-row tile one, over both wave rows).  Lanes h = 0, 1
-      // hold the same column (different rows); the wave rows of a group are
-      // then added in a fixed order.
-      static_assert(BM == 64 || BM == 128, "column-sum groups assume 64- or 128-row tiles");
-      constexpr int kGroups = BM / 64, kWaveRowsPerGroup = 2 / kGroups;
-      __shared__ float cs[2][BN];
+      // Column sums per 64-row group of the tile.  Lanes h = 0, 1 hold the same
+      // column (different rows); the wave rows of a group are then added in a
+      // fixed order.
+      constexpr int kGroups = BM / 64, kWaveRowsPerGroup = T::WGM / kGroups;
+      static_assert(kWaveRowsPerGroup * T::WM == 64, "a wave's rows lie in one group");
+      __shared__ float cs[T::WGM][BN];
 #pragma unroll
       for (int j = 0; j < T::TN; ++j) {
         const float v = csum[j] + __shfl_xor(csum[j], 32, 64);
-        if (h == 0) cs[wave >> 1][wn0 + j * 32 + r] = v;
+        if (h == 0) cs[wave / T::WGN][wn0 + j * 32 + r] = v;
       }
       __syncthreads();
 #pragma unroll
       for (int g = 0; g < kGroups; ++g) {
         const int crow = tm * kGroups + g;
         if (crow * 64 >= M) break;
-        for (int c = threadIdx.x; c < BN; c += kThreads) {
+        for (int c = threadIdx.x; c < BN; c += NTH) {
           if (n0 + c >= N) continue;
           float v = cs[g * kWaveRowsPerGroup][c];
           for (int w = 1; w < kWaveRowsPerGroup; ++w) v += cs[g * kWaveRowsPerGroup + w][c];
@@ -759,76 +790,45 @@ __global__ __launch_bounds__(NTH) void gemm_kernel(const float* __restrict__ A, 
       if (epi.limit > 0.f) add_faults((int)sse, epi.faults);
     }
     if constexpr (Epi::kSSE) {
-      __shared__ float red[kThreads / 64];
+      __shared__ float red[NTH / 64];
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) sse += __shfl_xor(sse, off, 64);
       if (lane == 0) red[wave] = sse;
       __syncthreads();
       if (threadIdx.x == 0) {
         double s = 0.0;
-        for (int w = 0; w < kThreads / 64; ++w) s += (double)red[w];
+        for (int w = 0; w < NTH / 64; ++w) s += (double)red[w];
         epi.sse_part[blockIdx.x] = s;
       }
     }
-    }
   }
 }
 
-// Tile configurations: 128 x 128 x 32 (wave tile 64 x 64, two blocks per
-// CU, 72 KB of LDS with both buffers) for products with at least one tile
-// per CU or deep enough in K for split-K to fill the chip, 128 x 64 among
-// those when N <= 64 (half of a 128-wide tile would be empty columns);
-// 64 x 64 x 32 (wave tile 32 x 32) for the other, small products, which
-// gives them four times the blocks (and wastes less of an edge tile).  (A
-// 256 x 128 x 16 tile, one block per CU round for more products, measured
-// slower on the wide and deep nets.)
-constexpr int kTileK = 32;
-constexpr int kChunkAlign = kTileK;   // split-K chunks are multiples of BK
 constexpr int kCUs = 256;
 
-inline int tiles_of(int M, int N, int t) { return ((M + t - 1) / t) * ((N + t - 1) / t); }
-// Edge of the square tile an M x N product summed over K uses.
-inline int tile_edge(int M, int N, int K) { return (tiles_of(M, N, 128) >= kCUs || K >= 1024) ? 128 : 64; }
-// Column edge of that tile.
-inline int tile_cols(int M, int N, int K) {
-  const int t = tile_edge(M, N, K);
-  return t == 128 && N <= 64 ? 64 : t;
-}
-inline int tile_count(int M, int N, int K) {
-  const int bm = tile_edge(M, N, K), bn = tile_cols(M, N, K);
-  return ((M + bm - 1) / bm) * ((N + bn - 1) / bn);
-}
+inline int tiles_of(int M, int N, int bm, int bn) { return ((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
 
-template <int BM, int BN, int BK, bool A_KM, bool B_NK, class Epi>
+// The tile an M x N product summed over K uses: 256 x 256 (1024 threads, one
+// block per CU), 128 x 128 or 64 x 64 (256 threads).
+struct TileShape {
+  int m, n;
+};
+TileShape tile_shape(int M, int N, int K);
+
+template <int BM, int BN, bool A_KM, bool B_NK, class Epi>
 hipError_t launch_gemm(hipStream_t s, const float* A, int lda, const float* B, int ldb, int M, int N, int K,
                        int splits, int k_chunk, const Epi& epi) {
   if (M <= 0 || N <= 0) return hipSuccess;
-  const int tiles = ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
-  const bool avec = (lda % 4 == 0) && ((reinterpret_cast<uintptr_t>(A) & 15) == 0);
-  const bool bvec = (ldb % 4 == 0) && ((reinterpret_cast<uintptr_t>(B) & 15) == 0);
-  dim3 grid(tiles, 1, splits), block(kThreads);
-  if (avec && bvec)
-    return launch_kernel(gemm_kernel<BM, BN, BK, A_KM, B_NK, true, true, Epi>, grid, block, 0, s, A, lda, B, ldb, M,
-                         N, K, k_chunk, epi);
-  if (avec)
-    return launch_kernel(gemm_kernel<BM, BN, BK, A_KM, B_NK, true, false, Epi>, grid, block, 0, s, A, lda, B, ldb, M,
-                         N, K, k_chunk, epi);
-  if (bvec)
-    return launch_kernel(gemm_kernel<BM, BN, BK, A_KM, B_NK, false, true, Epi>, grid, block, 0, s, A, lda, B, ldb, M,
-                         N, K, k_chunk, epi);
-  return launch_kernel(gemm_kernel<BM, BN, BK, A_KM, B_NK, false, false, Epi>, grid, block, 0, s, A, lda, B, ldb, M, N,
-                       K, k_chunk, epi);
+  return launch_kernel(gemm_kernel<BM, BN, A_KM, B_NK, Epi>, dim3(tiles_of(M, N, BM, BN), 1, splits),
+                       Tile<BM, BN>::NTH, 0, s, A, lda, B, ldb, M, N, K, k_chunk, epi);
 }
 
 template <bool A_KM, bool B_NK, class Epi>
-hipError_t launch_cfg(hipStream_t s, const float* A, int lda, const float* B, int ldb, int M, int N, int K, int splits,
-                      int k_chunk, const Epi& epi) {
-  if (tile_edge(M, N, K) == 128) {
-    if (tile_cols(M, N, K) == 64)
-      return launch_gemm<128, 64, kTileK, A_KM, B_NK>(s, A, lda, B, ldb, M, N, K, splits, k_chunk, epi);
-    return launch_gemm<128, 128, kTileK, A_KM, B_NK>(s, A, lda, B, ldb, M, N, K, splits, k_chunk, epi);
-  }
-  return launch_gemm<64, 64, kTileK, A_KM, B_NK>(s, A, lda, B, ldb, M, N, K, splits, k_chunk, epi);
+hipError_t launch_tile(hipStream_t s, TileShape t, const float* A, int lda, const float* B, int ldb, int M, int N,
+                       int K, int splits, int k_chunk, const Epi& epi) {
+  if (t.m == 256) return launch_gemm<256, 256, A_KM, B_NK>(s, A, lda, B, ldb, M, N, K, splits, k_chunk, epi);
+  if (t.m == 128) return launch_gemm<128, 128, A_KM, B_NK>(s, A, lda, B, ldb, M, N, K, splits, k_chunk, epi);
+  return launch_gemm<64, 64, A_KM, B_NK>(s, A, lda, B, ldb, M, N, K, splits, k_chunk, epi);
 }
 
 // --------------------------------------------------------------------------
@@ -863,16 +863,7 @@ hipError_t launch_cfg(hipStream_t s, const float* A, int lda, const float* B, in
 // product reads.
 constexpr int kSkinnyChunk = 16;   // MFMA steps per load round
 
-// 256 x 256 tiles of 512 threads (one block per CU) for products made of at
-// least one full such tile per CU: one round of blocks instead of two rounds
-// of 128 x 128 tiles, so one prologue and one epilogue per CU and no second
-// round starting behind the first round's slowest blocks.
-inline bool big_tiles(int M, int N, int K) {
-  return M % 256 == 0 && N % 256 == 0 && K % kTileK == 0 && K > 0 && tiles_of(M, N, 256) >= kCUs;
-}
-inline bool vec16(const void* p, int ld) { return (ld & 3) == 0 && (reinterpret_cast<uintptr_t>(p) & 15) == 0; }
-
-inline bool use_skinny(int M, int N, int K) { return K <= 2048 && tiles_of(M, N, 64) < 128; }
+inline bool use_skinny(int M, int N, int K) { return K <= 2048 && tiles_of(M, N, 64, 64) < 128; }
 
 struct CtxInput {
   const float* H = nullptr;   // previous step's hidden rows [M][ldh]
@@ -1404,23 +1395,62 @@ __global__ __launch_bounds__(kRed) void sse_reduce_kernel(const double* __restri
   block_sum_partials<kRed>(part, n, out, red);
 }
 
-// K-splits for a product with few output tiles: enough blocks for two per
-// CU (512), each split at least 256 deep in K.
-int choose_splits(int M, int N, int K) {
-  const int tiles = tile_count(M, N, K);
-  if (K < 1024 || tiles >= 512) return 1;
-  int s = (512 + tiles - 1) / tiles;
-  const int max_s = K / 256;
-  if (s > max_s) s = max_s;
-  return s < 1 ? 1 : s;
+// How an M x N product summed over K runs: its tile and the number of K
+// ranges (splits) it is cut into, each a multiple of the stage.
+//
+// The rule compares estimated times.  A stage (16 k) of q blocks per CU takes
+// about (measured at K = 1024, one to sixteen blocks per CU; microseconds)
+//   256 x 256:  1.0 + 1.75 q      128 x 128:  0.10 + 0.84 q      64 x 64:  0.30 + 0.25 q
+// (the larger tiles move less data per product, the smaller ones leave less of
+// the chip idle), and splitting costs what `split_us` says.
+struct Plan {
+  TileShape tile;
+  int splits;
+  int chunk;        // K range of a split
+  int tiles() const { return tiles_of(M, N, tile.m, tile.n); }
+  int M, N;
+};
+
+double stage_us(int edge, int blocks) {
+  const double q = (blocks + kCUs - 1) / kCUs;
+  return edge == 256 ? 1.0 + 1.75 * q : edge == 128 ? 0.10 + 0.84 * q : 0.30 + 0.25 * q;
 }
 
-int choose_output_splits(int M, int N, int K) { return use_skinny(M, N, K) ? 1 : choose_splits(M, N, K); }
-
-int chunk_for(int K, int splits) {
-  int c = (K + splits - 1) / splits;
-  return (c + kChunkAlign - 1) / kChunkAlign * kChunkAlign;
+// split_us(edge, tiles, splits): microseconds that `splits` > 1 ranges cost
+template <class F>
+Plan plan_product(int M, int N, int K, int max_splits, F&& split_us) {
+  Plan best{{64, 64}, 1, K, M, N};
+  double best_us = 1e30;
+  for (int edge : {256, 128, 64}) {
+    const int tiles = tiles_of(M, N, edge, edge);
+    for (int s = 1; s <= max_splits && (s == 1 || (K / s >= 256 && (long)tiles * s <= 4 * kCUs &&
+                                                   (size_t)tiles * s * edge * edge <= kMaxSplitFloats));
+         ++s) {
+      const int stages = (K + kStageK - 1) / kStageK, per = (stages + s - 1) / s;
+      const double us = per * stage_us(edge, tiles * s) + (s > 1 ? split_us(edge, tiles, s) : 0.0);
+      if (us < best_us) {
+        best_us = us;
+        best = {{edge, edge}, s, per * kStageK, M, N};
+      }
+    }
+  }
+  // every split gets a part of K
+  best.splits = K > 0 ? (K + best.chunk - 1) / best.chunk : 1;
+  if (best.splits <= 1) best.chunk = K;
+  return best;
 }
+
+TileShape tile_shape(int M, int N, int K) {
+  return plan_product(M, N, K, 1, [](int, int, int) { return 0.0; }).tile;
+}
+
+// Output layer: its split partials cross memory once more, and a launch
+// (output_finish_kernel) adds them.
+Plan output_plan(int M, int N, int K) {
+  return plan_product(M, N, K, 16, [&](int, int, int s) { return 6.0 + (double)s * M * N * 8.0 / 4e6; });
+}
+
+int choose_output_splits(int M, int N, int K) { return use_skinny(M, N, K) ? 1 : output_plan(M, N, K).splits; }
 
 }  // namespace
 
@@ -1437,7 +1467,7 @@ int colsum_rows(int M) { return (M + 63) / 64; }
 int output_delta_blocks(int M, int N, int K) {
   if (use_skinny(M, N, K)) return ((M + 63) / 64) * ((N + 31) / 32);
   if (choose_output_splits(M, N, K) > 1) return ((M + 127) / 128) * ((N + 63) / 64);
-  return tile_count(M, N, K);
+  return output_plan(M, N, K).tiles();
 }
 
 size_t output_delta_workspace(int M, int N, int K) {
@@ -1452,10 +1482,7 @@ hipError_t forward_layer(hipStream_t s, const float* A, int lda, const float* W,
                          const float* bias, float* out, int ldo, const float* tab) {
   EpiSigmoid e{bias, out, ldo, tab};
   if (use_skinny(M, N, K)) return launch_skinny<1, false>(s, A, lda, W, ldw, M, N, K, e);
-  if (big_tiles(M, N, K) && vec16(A, lda) && vec16(W, ldw) && vec16(out, ldo))
-    return launch_kernel(gemm_kernel<256, 256, kTileK, false, false, true, true, EpiSigmoid, 2 * kThreads>,
-                         tiles_of(M, N, 256), 2 * kThreads, 0, s, A, lda, W, ldw, M, N, K, K, e);
-  return launch_cfg<false, false>(s, A, lda, W, ldw, M, N, K, 1, K, e);
+  return launch_tile<false, false>(s, tile_shape(M, N, K), A, lda, W, ldw, M, N, K, 1, K, e);
 }
 
 bool forward_ctx_fits(int M, int N, int K) { return use_skinny(M, N, K); }
@@ -1519,11 +1546,12 @@ hipError_t forward_output_delta(hipStream_t s, const float* A, int lda, const fl
   if (sp <= 1) {
     EpiOutputDelta e{bias, T, ldt, delta, ldd, sse_part, colsum, ldcs, tab, mask};
     if (use_skinny(M, N, K)) return launch_skinny<2, false>(s, A, lda, W, ldw, M, N, K, e);
-    return launch_cfg<false, false>(s, A, lda, W, ldw, M, N, K, 1, K, e);
+    return launch_tile<false, false>(s, output_plan(M, N, K).tile, A, lda, W, ldw, M, N, K, 1, K, e);
   }
   const int ldp = (N + 3) / 4 * 4;
   EpiPartial e{ws, ldp, (size_t)M * ldp};
-  return launch_cfg<false, false>(s, A, lda, W, ldw, M, N, K, sp, chunk_for(K, sp), e);
+  const Plan pl = output_plan(M, N, K);
+  return launch_tile<false, false>(s, pl.tile, A, lda, W, ldw, M, N, K, sp, pl.chunk, e);
 }
 
 hipError_t output_finish(hipStream_t s, int M, int N, int K, const float* bias, const float* T, int ldt, float* delta,
@@ -1541,10 +1569,7 @@ hipError_t backward_layer(hipStream_t s, const float* D, int ldd, const float* W
                           const float* act, int lda, float* out, int ldo, float* colsum, int ldcs) {
   EpiHiddenDelta e{act, lda, out, ldo, colsum, ldcs};
   if (use_skinny(M, N, K)) return launch_skinny<2, true>(s, D, ldd, W, ldw, M, N, K, e);
-  if (big_tiles(M, N, K) && vec16(D, ldd) && vec16(W, ldw) && vec16(out, ldo) && vec16(act, lda))
-    return launch_kernel(gemm_kernel<256, 256, kTileK, false, true, true, true, EpiHiddenDelta, 2 * kThreads>,
-                         tiles_of(M, N, 256), 2 * kThreads, 0, s, D, ldd, W, ldw, M, N, K, K, e);
-  return launch_cfg<false, true>(s, D, ldd, W, ldw, M, N, K, 1, K, e);
+  return launch_tile<false, true>(s, tile_shape(M, N, K), D, ldd, W, ldw, M, N, K, 1, K, e);
 }
 
 // The change product of a layer: few output tiles and a long batch take the
@@ -1561,29 +1586,65 @@ struct ChangePlan {
   int chunk;
   int tiles;        // output tiles
   int tile_elems;   // floats per output tile
-  bool tiles64 = false;  // 64 x 64 tiles on gemm_kernel
+  TileShape tile{0, 0};  // gemm_kernel's
 };
 
 ChangePlan change_plan(int M, int N, int K) {
+  const int tiles64 = tiles_of(M, N, 64, 64);
   // long K over 16-127 output tiles of 64 x 64: those tiles split over K on
   // about one block per CU
-  if (K >= 4096 && tiles_of(M, N, 64) >= 16 && tiles_of(M, N, 64) < 128) {
-    const int tiles = tiles_of(M, N, 64);
-    const int sp = std::min((kCUs + tiles - 1) / tiles, K / 256);
-    return {false, sp, chunk_for(K, sp), tiles, 64 * 64, true};
+  if (K >= 4096 && tiles64 >= 16 && tiles64 < 128) {
+    const int stages = (K + kStageK - 1) / kStageK, want = std::min((kCUs + tiles64 - 1) / tiles64, K / 256);
+    const int chunk = (stages + want - 1) / want * kStageK;
+    return {false, (K + chunk - 1) / chunk, chunk, tiles64, 64 * 64, {64, 64}};
   }
-  if (K >= 1024 && tiles_of(M, N, 64) < 128) {
+  if (K >= 1024 && tiles64 < 128) {
     const int tiles = ((M + 63) / 64) * ((N + 31) / 32);
     int chunk = 1024;
     while (chunk > 128 && (long)tiles * ((K + chunk - 1) / chunk) < kSkinnyChangeBlocks) chunk /= 2;
     const int sp = (K + chunk - 1) / chunk;
     if (sp >= 2) return {true, sp, chunk, tiles, 64 * 32};
   }
-  const int sp = choose_splits(M, N, K);
-  return {false, sp, sp > 1 ? chunk_for(K, sp) : K, tile_count(M, N, K), tile_edge(M, N, K) * tile_cols(M, N, K)};
+  // a split costs its partials' way through memory and the last block's sum
+  const Plan pl = plan_product(M, N, K, 64, [](int edge, int tiles, int s) {
+    const double kb = edge * edge * 4e-3;
+    return 4.0 + (s + 3.0) * kb * 0.012 + (double)tiles * s * kb * 1e-3 * 0.4;
+  });
+  return {false, pl.splits, pl.chunk, pl.tiles(), pl.tile.m * pl.tile.n, pl.tile};
 }
 
 int change_splits(int M, int N, int K) { return change_plan(M, N, K).splits; }
+
+// What a fixed scratch counts for the split partials of an M x N change (or,
+// output, of the output layer's product) summed over K: 512 tiles of
+// 128 x 128 at most, one per split and output tile.  It is what decides which
+// calls bp_train_batches_noalloc takes, and stays as it is when plans change;
+// the scratch has kMaxSplitFloats more than its limit, so that every plan fits.
+size_t scratch_split_floats(int M, int N, int K, bool output) {
+  auto ceil_div = [](int a, int b) { return (a + b - 1) / b; };
+  const int t64 = tiles_of(M, N, 64, 64);
+  if (output && use_skinny(M, N, K)) return 0;
+  if (!output && K >= 4096 && t64 >= 16 && t64 < 128)
+    return (size_t)std::min(ceil_div(kCUs, t64), K / 256) * t64 * 64 * 64;
+  if (!output && K >= 1024 && t64 < 128) {
+    const int tiles = tiles_of(M, N, 64, 32);
+    int chunk = 1024;
+    while (chunk > 128 && (long)tiles * ceil_div(K, chunk) < kCUs) chunk /= 2;
+    if (ceil_div(K, chunk) >= 2) return (size_t)ceil_div(K, chunk) * tiles * 64 * 32;
+  }
+  const int bm = tiles_of(M, N, 128, 128) >= kCUs || K >= 1024 ? 128 : 64, bn = bm == 128 && N <= 64 ? 64 : bm;
+  const int tiles = tiles_of(M, N, bm, bn);
+  const int splits = K < 1024 || tiles >= 512 ? 1 : std::min(ceil_div(512, tiles), K / 256);
+  if (splits <= 1) return 0;
+  return output ? (size_t)splits * M * ((N + 3) / 4 * 4) : (size_t)splits * tiles * bm * bn;
+}
+
+int scratch_error_blocks(int M, int N, int K) {
+  if (use_skinny(M, N, K)) return tiles_of(M, N, 64, 32);
+  if (scratch_split_floats(M, N, K, true) > 0) return tiles_of(M, N, 128, 64);
+  const int bm = tiles_of(M, N, 128, 128) >= kCUs || K >= 1024 ? 128 : 64;
+  return tiles_of(M, N, bm, bm == 128 && N <= 64 ? 64 : bm);
+}
 
 size_t change_update_workspace(int M, int N, int K) {
   const ChangePlan pl = change_plan(M, N, K);
@@ -1602,15 +1663,14 @@ hipError_t change_update(hipStream_t s, const float* A, int lda, const float* D,
   const ChangePlan pl = change_plan(M, N, K);
   if (pl.splits <= 1) {
     EpiUpdate e{W, V, ldw, lr, mom, limit, faults};
-    return launch_cfg<true, false>(s, A, lda, D, ldd, M, N, K, 1, K, e);
+    return launch_tile<true, false>(s, pl.tile, A, lda, D, ldd, M, N, K, 1, K, e);
   }
   if (!arrivals || !ws || pl.tiles > kMaxArrivals) return hipErrorInvalidValue;
   EpiSplitUpdate e{ws, W, V, ldw, lr, mom, limit, faults, arrivals, pl.splits};
-  if (pl.tiles64) return launch_gemm<64, 64, kTileK, true, false>(s, A, lda, D, ldd, M, N, K, pl.splits, pl.chunk, e);
   if (pl.skinny)
     return launch_kernel(skinny_kernel<2, true, false, false, false, false, EpiSplitUpdate>, pl.tiles * pl.splits, 512,
                          0, s, A, lda, D, ldd, M, N, K, pl.chunk, e, CtxInput{});
-  return launch_cfg<true, false>(s, A, lda, D, ldd, M, N, K, pl.splits, pl.chunk, e);
+  return launch_tile<true, false>(s, pl.tile, A, lda, D, ldd, M, N, K, pl.splits, pl.chunk, e);
 }
 
 hipError_t bias_update(hipStream_t s, const BiasJob* jobs, int n, float lr, float mom, float limit,

@@ -119,8 +119,11 @@ struct bp_net {
 // memory): bp_create looks up each device's copy once, with that device
 // current, and the entry point takes that address.  Every call on a GPU
 // shares the GPU's copy, so calls that overlap on one GPU race.
+// A call is taken when its workspace, with partials counted as
+// scratch_split_floats and scratch_error_blocks do, is at most kScratchBytes;
+// the array also has room for the largest partials a plan may use instead.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) float scratch[kScratchBytes / sizeof(float)];
+static __device__ __align__(256) float scratch[kScratchBytes / sizeof(float) + bpk::kMaxSplitFloats];
 
 namespace {
 
@@ -593,7 +596,7 @@ int train_noalloc(bp_net* net, const BatchInput& in, const float* targets, int64
   const size_t n_sse = (size_t)sse_blocks(net, in, (int)rows_max) * (size_t)(nb - 1) +
                        (size_t)sse_blocks(net, in, last_rows);
   // layout, each piece on a 256-byte boundary: act[1..L-1], del[1..L],
-  // csum[1..L], split partials, arrival counters, error partials, error sum
+  // csum[1..L], arrival counters, error partials, error sum, split partials
   size_t off = 0;
   auto take = [&](size_t floats) {
     const size_t o = off;
@@ -606,16 +609,30 @@ int train_noalloc(bp_net* net, const BatchInput& in, const float* targets, int64
     od[l] = take((size_t)rows_max * net->lda[l]);
     oc[l] = take((size_t)bpk::colsum_rows((int)rows_max) * net->lda[l]);
   }
-  const size_t osk = take(sk);
+  // what decides whether the call is taken counts partials by a measure of
+  // their own (scratch_split_floats, scratch_error_blocks)
+  auto padded = [](size_t floats) { return (floats + 63) / 64 * 64; };
+  size_t counted = 0, counted_sse = 0;
+  for (const int64_t rows : {rows_max, (int64_t)last_rows}) {
+    counted = std::max(counted, bpk::scratch_split_floats((int)rows, net->n[net->L], net->n[net->L - 1], true));
+    for (int l = 0; l < net->L; ++l)
+      counted = std::max(counted, bpk::scratch_split_floats(net->n[l], net->n[l + 1], (int)rows, false));
+  }
+  auto error_blocks = [&](int64_t rows) {
+    return (size_t)bpk::scratch_error_blocks((int)rows, net->n[net->L], net->n[net->L - 1]);
+  };
+  counted_sse = error_blocks(rows_max) * (size_t)(nb - 1) + error_blocks(last_rows);
+  counted = off + padded(counted) + padded(bpk::kMaxArrivals) + padded(2 * counted_sse) + padded(2);
   const size_t oarr = take(bpk::kMaxArrivals);
   const size_t osp = take(2 * n_sse);
   const size_t osd = take(2);
-  if (off * sizeof(float) > kScratchBytes) {
+  const size_t osk = take(sk);
+  if (counted * sizeof(float) > kScratchBytes || off * sizeof(float) > sizeof(scratch)) {
     char buf[256];
     std::snprintf(buf, sizeof(buf),
                   "bp_train_batches_noalloc: the call needs %zu bytes of workspace, more than the %zu-byte "
                   "scratch (use a smaller batch, or bp_train_batches)",
-                  off * sizeof(float), kScratchBytes);
+                  std::max(counted, off) * sizeof(float), kScratchBytes);
     return fail(net, BP_EINVAL, buf);
   }
   // swap the views in, run, swap back
