@@ -265,6 +265,17 @@ hipError_t elman_window(hipStream_t s, const ElmanWindow& w);
 // out[0] = sum of part[0 .. n-1] in a fixed order (double).
 hipError_t sse_reduce(hipStream_t s, const double* part, int n, double* out);
 
+// Floats [first, first + n) of a net's flat weight layout (layers one after
+// the other, row-major without padding) between `flat` (element 0 = float
+// `first`; device-visible memory) and the layers' padded rows.
+struct FlatLayer {
+  float* dev;              // [rows][ld]
+  int64_t off;             // the layer's first float in the flat layout
+  int rows, cols, ld;
+};
+hipError_t copy_flat(hipStream_t s, const FlatLayer* layers, int n_layers, int64_t first, int64_t n, float* flat,
+                     bool to_layers);
+
 // Sets p[0, n) to zero with a kernel (no memset node when captured).
 hipError_t zero_ints(hipStream_t s, int* p, int n);
 

@@ -266,3 +266,26 @@ def test_option_arguments_are_checked(dev):
             bad()
         assert e.value.code == bp.BP_EINVAL
     assert net.fault_count() == 0
+
+
+@pytest.mark.parametrize("sizes", [(1, 1), (3, 5, 7, 2), (5, 31, 33, 1, 4, 6, 2, 9, 3, 8, 2), (1500, 1501), (300, 4099, 700)])
+def test_state_copies_round_trip(dev, sizes):
+    """Weights and momentum through the padded device rows and back, bit for bit: one float, more layers than one copy
+    launch takes, a state of more than one piece (2 M floats), pieces that end inside a row."""
+    print(f"state copies: sizes={sizes}", flush=True)
+    net = bp.Net(sizes)
+    try:
+        g = np.random.default_rng(sum(sizes))
+        w = g.standard_normal(net.n_weights).astype(np.float32)
+        v = g.standard_normal(net.n_weights).astype(np.float32)
+        net.set_weights(w)
+        assert not net.get_momentum().any()
+        net.set_momentum(v)
+        for _ in range(2):
+            assert np.array_equal(net.get_weights(), w)
+            assert np.array_equal(net.get_momentum(), v)
+        net.set_weights(v)
+        assert np.array_equal(net.get_weights(), v)
+        assert not net.get_momentum().any()
+    finally:
+        net.close()
