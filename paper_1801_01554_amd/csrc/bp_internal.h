@@ -163,11 +163,12 @@ hipError_t onehot_forward(hipStream_t s, const int32_t* act, int n_active, int r
                           int n0, int H, int mode, float* out, int ldo, const float* T, int ldt,
                           double* sse_part, const float* tab);
 
-// One-hot first-layer change and update for all n0 + 1 rows:
+// One-hot first-layer change and update of the n0 weight rows and, with
+// `bias_row`, the bias row (D rows 16-byte aligned, ldd a multiple of 4):
 //   G[r][j] = sum over patterns p containing index r of D[p][j]  (r < n0),
 //   G[n0][j] = sum_p D[p][j];  V = lr G + mom V;  W += V.
-hipError_t onehot_update(hipStream_t s, const int32_t* act, int n_active, int rows, const float* D, int ldd,
-                         int n0, int H, float* W, float* V, int ldw, float lr, float mom, float limit,
+hipError_t onehot_update(hipStream_t s, const int32_t* act, int n_active, int rows, const float* D, int ldd, int n0,
+                         int H, bool bias_row, float* W, float* V, int ldw, float lr, float mom, float limit,
                          unsigned long long* faults);
 
 // ---- fused path for small two-layer nets with one-hot inputs (bp_small.hip)

@@ -487,18 +487,22 @@ int run_backward_update(bp_net* net, const BatchInput& in, int rows, float lr, f
                                     net->n[l + 1], net->act[l], net->lda[l], net->del[l], net->lda[l], net->csum[l],
                                     net->lda[l]));
     if (l == 0 && in.act) {
+      // the bias row is the sum of the deltas' column sums, which a one-layer
+      // net's output kernel does not write
       BP_LAUNCH(net, BP_K_SCATTER,
                 bpk::onehot_update(s, in.act, in.n_active, rows, net->del[1], net->lda[1], net->n[0], net->n[1],
-                                   wl(net, 0), vl(net, 0), net->ldw[0], lr, mom, net->fault_limit, net->faults));
-      continue;
+                                   net->L == 1, wl(net, 0), vl(net, 0), net->ldw[0], lr, mom, net->fault_limit,
+                                   net->faults));
+      if (net->L == 1) continue;
+    } else {
+      const float* A = (l == 0) ? in.x : net->act[l];
+      const int ldA = (l == 0) ? ldx_of(net, in) : net->lda[l];
+      const bool split = bpk::change_splits(net->n[l], net->n[l + 1], rows) > 1;
+      BP_LAUNCH(net, split ? BP_K_SPLITK : BP_K_CHANGE,
+                bpk::change_update(s, A, ldA, net->del[l + 1], net->lda[l + 1], net->n[l], net->n[l + 1], rows,
+                                   wl(net, l), vl(net, l), net->ldw[l], lr, mom, net->splitk, net->arrivals,
+                                   net->fault_limit, net->faults));
     }
-    const float* A = (l == 0) ? in.x : net->act[l];
-    const int ldA = (l == 0) ? ldx_of(net, in) : net->lda[l];
-    const bool split = bpk::change_splits(net->n[l], net->n[l + 1], rows) > 1;
-    BP_LAUNCH(net, split ? BP_K_SPLITK : BP_K_CHANGE,
-              bpk::change_update(s, A, ldA, net->del[l + 1], net->lda[l + 1], net->n[l], net->n[l + 1], rows,
-                                 wl(net, l), vl(net, l), net->ldw[l], lr, mom, net->splitk, net->arrivals,
-                                 net->fault_limit, net->faults));
     bias[nb++] = {net->csum[l + 1], wbias(net, l), vbias(net, l), net->lda[l + 1],
                   (l + 1 == net->L && top_csum > 0) ? top_csum : bpk::colsum_rows(rows), net->n[l + 1], 0};
     if (nb == bpk::kMaxBiasJobs) {

@@ -130,3 +130,55 @@ def test_operands_that_are_not_finite(rows, n_in, n_out):
     # rows and columns that hold the large values saturate
     err = (got - y).abs()
     assert bool((err[ok] <= (0.25 * _bound(n_in, S) + 4 * U)[ok]).all())
+
+
+# inputs, layer sizes above, patterns, active inputs: widths around one lane's
+# four columns, a wave's 256 and a block's 1024; lists that are empty, shorter
+# than their slices, or span several 1024-pattern chunks; more active inputs
+# than rows in flight; indices past one round of 16384; one layer (bias row in
+# the scatter kernel) and two
+@pytest.mark.parametrize("sizes,rows,n_active", [
+    ((40, 3), 70, 1), ((40, 5, 4), 1023, 10), ((60, 257, 9), 1025, 11), ((300, 65), 2100, 33), ((9, 1027, 3), 513, 7),
+    ((2000, 300, 70), 64, 3), ((50, 70, 5), 4000, 13),
+])
+@pytest.mark.parametrize("checked", [False, True])
+def test_onehot_rows(sizes, rows, n_active, checked):
+    print(f"one-hot rows: sizes={sizes} rows={rows} active={n_active} checked={checked}", flush=True)
+    g = np.random.default_rng(rows)
+    act = np.stack([g.permutation(sizes[0])[:n_active] for _ in range(rows)]).astype(np.int32)
+    act[rows // 2, 0] = -1                    # selects no row
+    act[rows - 1, n_active - 1] = sizes[0]    # neither does this
+    w = wl.draw_weights(9, sizes, "uniform0.3")
+    t = torch.from_numpy(g.uniform(0.1, 0.9, (rows, sizes[-1])).astype(np.float32)).cuda()
+    W, o = [], 0
+    for a, b in zip(sizes[:-1], sizes[1:]):
+        W.append(torch.from_numpy(w[o:o + (a + 1) * b].astype(np.float64)).view(a + 1, b).cuda())
+        o += (a + 1) * b
+    x = torch.zeros((rows, sizes[0] + 2), dtype=torch.float64, device="cuda")
+    a64 = torch.from_numpy(act).cuda().long()
+    x.scatter_(1, torch.where(a64 < 0, sizes[0] + 1, a64), 1.0)
+    acts = [x[:, :sizes[0]]]
+    for m in W:
+        acts.append(torch.sigmoid(acts[-1] @ m[:-1] + m[-1]))
+    net = bp.Net(sizes)
+    try:
+        net.set_weights(w)
+        if checked:
+            net.set_fault_limit(1e6)
+        dact = torch.from_numpy(act).cuda()
+        y = net.forward(active=dact).double()
+        assert float((y - acts[-1]).abs().max()) < 1e-6
+        net.train_batches(t, rows, 1.0, 0.0, active=dact)
+        V = torch.from_numpy(net.get_momentum().astype(np.float64)).cuda()
+        if checked:
+            assert net.fault_count() == 0
+    finally:
+        net.close()
+    d = (t.double() - acts[-1]) * acts[-1] * (1 - acts[-1])
+    for l in range(len(W) - 1, -1, -1):
+        G = torch.cat([acts[l].T @ d, d.sum(0, keepdim=True)])
+        o -= G.numel()
+        got = V[o:o + G.numel()].view_as(G)
+        assert float((got - G).abs().max() / G.abs().max()) < 5e-6, l     # fp32 sums of at most `rows` terms
+        assert bool((got[:-1][(acts[l] != 0).sum(0) == 0] == 0).all())    # rows no pattern has stay put
+        d = (d @ W[l][:-1].T) * acts[l] * (1 - acts[l])
