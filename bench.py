@@ -56,8 +56,8 @@ KERNEL_NAMES = {
     "output": "gemm_kernel|skinny_kernel<..., EpiOutputDelta>",
     "backward": "gemm_kernel|skinny_kernel<..., EpiHiddenDelta>",
     "change": "gemm_kernel<..., EpiUpdate>",
-    "splitk": "gemm_kernel|skinny_kernel<..., EpiSplitUpdate>",
-    "bias": "bias_update_kernel",
+    "splitk": "gemm_kernel|skinny_kernel<..., EpiChangePartial>",
+    "bias": "update_finish_kernel",
     "gather": "onehot_forward_kernel",
     "scatter": "onehot_update_kernel",
     "reduce": "sse_reduce_kernel",
@@ -196,28 +196,41 @@ def elman_window(sizes, n_ctx, S):
 
 
 def change_splits(M, N, K):
-    """Mirror of the library's split count for a change product (split over blocks, whose last
-    block per tile applies the update), for work accounting only."""
-    t64 = -(-M // 64) * -(-N // 64)
-    if K >= 4096 and 16 <= t64 < 128:
-        return min(-(-256 // t64), K // 256)
-    if K >= 1024 and -(-M // 64) * -(-N // 64) < 128:
-        tiles, chunk = -(-M // 64) * -(-N // 32), 1024
-        while chunk > 128 and tiles * -(-K // chunk) < 256:
-            chunk //= 2
-        if -(-K // chunk) >= 2:
-            return -(-K // chunk)
-    return choose_splits(M, N, K)
+    """Mirror of the library's plan for a change product, for work accounting only: the number of K
+    ranges whose partials a later launch adds, 1 if the product applies the update itself."""
+    def split_us(s):
+        return 3.0 + s * M * N * 8.0 / 4e6
+
+    splits, us = plan_product(M, N, K, 64, lambda s: split_us(s) if s > 1 else 5.0)
+    tiles = -(-M // 64) * -(-N // 32)
+    if tiles <= 128:
+        want = max(1, min(256 // tiles, K // 128))
+        chunk = -(-(-(-K // want)) // 32) * 32
+        n = max(1, -(-K // chunk))
+        if 4.0 + 0.0135 * chunk + split_us(n) < us:
+            return max(2, n)      # partials even when there is one
+    return splits
 
 
 def choose_splits(M, N, K):
-    """Mirror of the library's split-K choice, for work accounting only."""
-    t128 = -(-M // 128) * -(-N // 128)
-    tiles = t128 if (t128 >= 256 or K >= 1024) else -(-M // 64) * -(-N // 64)
-    if K < 1024 or tiles >= 512:
-        return 1
-    s = -(-512 // tiles)
-    return max(1, min(s, K // 256))
+    """Mirror of the library's split-K choice for an output layer, for work accounting only."""
+    return plan_product(M, N, K, 16, lambda s: 6.0 + s * M * N * 8.0 / 4e6 if s > 1 else 0.0)[0]
+
+
+def plan_product(M, N, K, max_splits, split_us):
+    """Mirror of the library's estimate: (splits, microseconds) of the fastest tile and split."""
+    best, stages = (1, float("inf")), -(-K // 16)
+    for edge in (256, 128, 64):
+        tiles = -(-M // edge) * -(-N // edge)
+        for s in range(1, max_splits + 1):
+            if s > 1 and (K // s < 96 or tiles * s > 1024 or tiles * s * edge * edge > 16 << 20):
+                break
+            q, per = -(-tiles * s // 256), -(-stages // s)
+            stage = 1.0 + 1.75 * q if edge == 256 else 0.10 + 0.84 * q if edge == 128 else 0.30 + 0.25 * q
+            us = 5.0 + per * stage + split_us(s)
+            if us < best[1]:
+                best = (-(-K // (per * 16)) if K else 1, us)
+    return best
 
 
 def schedule(spec, steps):
@@ -456,7 +469,10 @@ def kind_of_kernel(name):
     m = re.search(r"(gemm_kernel|skinny_kernel)<[^>]*?\b(Epi\w+)", name)
     if m:
         return {"EpiSigmoid": "forward", "EpiOutputDelta": "output", "EpiPartial": "output",
-                "EpiHiddenDelta": "backward", "EpiUpdate": "change", "EpiSplitUpdate": "splitk"}.get(m.group(2))
+                "EpiHiddenDelta": "backward", "EpiUpdate": "change", "EpiChangePartial": "splitk",
+                "EpiSplitUpdate": "splitk"}.get(m.group(2))   # (the last: profiles of earlier versions)
+    if "bias_update_kernel" in name:                           # (likewise)
+        return "bias"
     for k, v in KERNEL_NAMES.items():
         if "<" not in v and v in name:
             return k

@@ -118,7 +118,7 @@ int bp_train_batches(bp_net* net, const float* inputs_dev, const float* targets_
  * under HIP graph capture, tight serving loops, harnesses that forbid
  * allocation): same arguments, same launches and the same results, bit for
  * bit.  The call's workspace (activations, deltas, column sums, split-K
- * partials and counters, error partials) lives in a fixed 64 MiB array per
+ * partials, error partials) lives in a fixed 64 MiB array per
  * GPU, held by the library until the process ends, instead of in the net's
  * own allocations; nothing is allocated or freed, and no graph is captured
  * (every launch is issued directly).  The array is shared by every net and
@@ -255,10 +255,10 @@ enum {
   BP_K_OUTPUT = 1,    /* output-layer forward product + deltas + error      */
   BP_K_BACKWARD = 2,  /* hidden-delta product + derivative                  */
   BP_K_CHANGE = 3,    /* summed-change product + momentum update           */
-  BP_K_SPLITK = 4,    /* summed-change product split over the batch; the  */
-                      /* last block of each tile adds the partials in     */
-                      /* split order and applies the momentum update      */
-  BP_K_BIAS = 5,      /* bias-row column sums + momentum update             */
+  BP_K_SPLITK = 4,    /* summed-change product split over the batch        */
+                      /* (partial sums, added and applied by BP_K_BIAS)    */
+  BP_K_BIAS = 5,      /* end of an update: bias rows' column sums and split */
+                      /* changes' partials in split order + momentum update */
   BP_K_GATHER = 6,    /* one-hot first-layer forward                        */
   BP_K_SCATTER = 7,   /* one-hot first-layer change + momentum update       */
   BP_K_REDUCE = 8,    /* epoch error reduction                              */

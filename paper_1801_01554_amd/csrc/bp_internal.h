@@ -100,15 +100,10 @@ hipError_t output_finish(hipStream_t s, int M, int N, int K, const float* bias, 
 hipError_t backward_layer(hipStream_t s, const float* D, int ldd, const float* W, int ldw, int M, int N,
                           int K, const float* act, int lda, float* out, int ldo, float* colsum, int ldcs);
 
-// Number of K-splits change_update uses for an M x N change summed over K
-// rows (1 = one block per output tile applies the update from its
-// accumulators).
-int change_splits(int M, int N, int K);
+// Floats of partials change_product of an M x N change over K rows leaves (0: it applies the update itself).
+size_t change_partial_floats(int M, int N, int K);
 
-// Floats of split workspace change_update needs for an M x N change summed over K rows.
-size_t change_update_workspace(int M, int N, int K);
-
-// Most floats of partials any split product (change or output layer) uses.
+// Most floats of partials any one product (change or output layer) uses.
 constexpr size_t kMaxSplitFloats = (size_t)16 << 20;
 // Floats that a fixed scratch counts for the partials of an M x N change
 // (output: of the output layer's product) summed over K.
@@ -116,23 +111,22 @@ size_t scratch_split_floats(int M, int N, int K, bool output);
 // Error partials it counts for an output layer.
 int scratch_error_blocks(int M, int N, int K);
 
-// Arrival counters (one per output tile) a split change_update of an M x N
-// change summed over K rows uses; 0 when it is not split.  Never more than
-// kMaxArrivals: a product is split only when it has fewer output tiles than
-// that.
-constexpr int kMaxArrivals = 512;
-int change_arrivals(int M, int N, int K);
-
 // Weight change and update for the non-bias rows:
 //   G[m][n] = sum_k A[k][m] D[k][n];  V = lr G + mom V;  W += V   (m < M, n < N).
-// With change_splits(M, N, K) > 1 the blocks of each output tile write their
-// partial sums to `ws` (change_update_workspace floats) and the last one to
-// arrive adds them in split order and applies the update, counting arrivals
-// in `arrivals` (kMaxArrivals ints, all zero before the launch and left zero
-// after it; launches that use them must not overlap).
-hipError_t change_update(hipStream_t s, const float* A, int lda, const float* D, int ldd, int M, int N,
-                         int K, float* W, float* V, int ldw, float lr, float mom, float* ws, int* arrivals,
-                         float limit, unsigned long long* faults);
+// With change_partial_floats(M, N, K) > 0 the product writes its partial sums
+// to `partials` (that many floats) and fills in `job`, and the update happens
+// when finish_update is given that job.
+struct ChangeJob {
+  const float* P;   // [splits][M][ldp]
+  float* W;
+  float* V;
+  size_t stride;    // floats between splits
+  int splits, M, N, ldp, ldw;
+  int block0;       // set by finish_update
+};
+hipError_t change_product(hipStream_t s, const float* A, int lda, const float* D, int ldd, int M, int N, int K,
+                          float* W, float* V, int ldw, float lr, float mom, float limit, unsigned long long* faults,
+                          float* partials, ChangeJob* job);
 
 // Bias-row change and update of one layer: G[n] = sum_{k < rows} D[k][n];
 // V = lr G + mom V;  W += V.  D is the per-tile column-sum buffer of the
@@ -142,17 +136,20 @@ struct BiasJob {
   float* Wb;
   float* Vb;
   int ldd, rows, N;
-  int block0;   // set by bias_update
+  int block0;   // set by finish_update
 };
-constexpr int kMaxBiasJobs = 8;
-struct BiasJobs {
-  BiasJob j[kMaxBiasJobs];
-  int n;
+constexpr int kMaxFinishJobs = 8;
+struct FinishJobs {
+  BiasJob bias[kMaxFinishJobs];
+  ChangeJob change[kMaxFinishJobs];
+  int n_bias, n_change;
+  int change_block0;   // blocks below it take bias jobs
 };
-// The bias updates of n layers (independent: distinct D, Wb, Vb), up to
-// kMaxBiasJobs per launch.
-hipError_t bias_update(hipStream_t s, const BiasJob* jobs, int n, float lr, float mom, float limit,
-                       unsigned long long* faults);
+// The bias updates of n_bias layers and the updates of n_change split change
+// products (independent: distinct D, P, W, V), up to kMaxFinishJobs of each
+// per launch.
+hipError_t finish_update(hipStream_t s, const BiasJob* bias, int n_bias, const ChangeJob* change, int n_change,
+                         float lr, float mom, float limit, unsigned long long* faults);
 
 // One-hot first layer: net[p][j] = W0[n0][j] + sum_{k < n_active} W0[act[p][k]][j].
 // mode 0: out[p][j] = sigma(net).  mode 1 (single-layer nets, training):
@@ -276,8 +273,5 @@ struct FlatLayer {
 };
 hipError_t copy_flat(hipStream_t s, const FlatLayer* layers, int n_layers, int64_t first, int64_t n, float* flat,
                      bool to_layers);
-
-// Sets p[0, n) to zero with a kernel (no memset node when captured).
-hipError_t zero_ints(hipStream_t s, int* p, int n);
 
 }  // namespace bpk

@@ -141,10 +141,12 @@ struct EpiUpdate {
   }
 };
 
-// Split-K partial: P[z][m][n] for z = blockIdx.z.
+// Split-K partial: out[z][m][n] for z = blockIdx.z.  The partials of a change
+// product (EpiChangePartial) are added, in split order, by update_finish_kernel, which
+// then applies the update; those of the output layer by output_finish_kernel.
 struct EpiPartial {
-  float* P;
-  int ldp;
+  float* out;
+  int ldo;
   size_t split_stride;
   static constexpr bool kSSE = false;
   static constexpr bool kColSum = false;
@@ -153,103 +155,11 @@ struct EpiPartial {
   __device__ Pre load(int, int) const { return {}; }
   __device__ float column(int) const { return 0.f; }
   __device__ float apply(int m, int n, float acc, float, Pre, float&) const {
-    P[blockIdx.z * split_stride + (size_t)m * ldp + n] = acc;
+    out[blockIdx.z * split_stride + (size_t)m * ldo + n] = acc;
     return 0.f;
   }
 };
-
-// Split-K change product fused with the update (the update routine of
-// section 6.2.1 applied to the batch-summed change).  The blocks of one
-// output tile each sum one K range of the batch.  Every block stores its
-// partial sums and counts its arrival (one counter per output tile); the
-// block that arrives last adds the tile's partials in split order, taking
-// its own from registers, and applies the range check and the momentum
-// update to them, as the epilogue of an unsplit product does.  The sum does
-// not depend on which block arrives last (results are run-to-run identical)
-// and the summed change itself never reaches memory.
-//
-// Partials are stored in the accumulator layout, lane fastest: 4-float slot
-// u of lane l in wave w of block (tile t, split z) is at float offset
-//   (((z * tiles + t) * waves + w) * slots + u) * 256 + 4 l,
-// so every store or load instruction of a wave covers 1 KB of contiguous
-// memory.  They are written and read with the device-coherent cache policy
-// (written through the L2 of the XCD, read from the coherent level), so
-// blocks on different XCDs see each other's partials without a fence (a
-// device-scope fence would write back, or drop, the whole L2 of the XCD).
-struct EpiSplitUpdate {
-  float* P;                         // partials (split_workspace floats)
-  float* W;
-  float* V;
-  int ldw;
-  float lr, mom;
-  float limit;                      // range check of the summed change (> 0: on)
-  unsigned long long* faults;
-  int* arrivals;                    // per output tile; zero before and after every launch
-  int splits;
-  static constexpr bool kColSum = false;
-  static constexpr bool kFaults = true;
-};
-
-constexpr int kCoherent = 16;       // buffer cache policy bit sc1: device-coherent access
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t partial_rsrc(float* base) {
-  return __builtin_amdgcn_make_buffer_rsrc(base, (short)0, 0x7fffffff, 0x00020000);
-}
-
-// Every thread of the block calls this after storing its partial slots.
-// Each wave waits until its stores are complete (performed at the coherent
-// level) before the block's arrival is counted.  Returns true, in every
-// thread, in the block that arrives last at `tile`; that block also resets
-// the tile's counter for the next launch.
-__device__ __forceinline__ bool split_arrive(const EpiSplitUpdate& e, int tile) {
-  __shared__ int last;
-  __builtin_amdgcn_s_waitcnt(0x0f70);   // vmcnt(0): this wave's partial stores are complete
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    const bool l =
-        __hip_atomic_fetch_add(e.arrivals + tile, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == e.splits - 1;
-    if (l) __hip_atomic_store(e.arrivals + tile, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    last = l;
-  }
-  __syncthreads();
-  return last;
-}
-
-// g[u] = the sum over splits 0 .. S-1, in split order, of this lane's slot
-// `slot0 + u` (split z's own value from `own`).  `r` addresses split 0 of
-// the block's partials; splits are `zstride` bytes apart, slots 1 KB.  The
-// other splits' slots are loaded in groups of ZB splits, all in flight
-// together: by default one split at a time for 4 slots (a 32 x 32 block of
-// 128-row tiles of gemm_kernel: more would cost it its second wave per
-// SIMD), 16 splits for one slot.  The 64 x 64 tiles, launched about one
-// block per CU, load 8 splits at a time (Elman epoch 1.3% faster).
-template <int NS, int ZB = (NS >= 4 ? 1 : 16 / NS)>   // ZB: splits per load group
-__device__ __forceinline__ void ordered_split_sum(f32x4 (&g)[NS], const f32x4 (&own)[NS], __amdgpu_buffer_rsrc_t r,
-                                                  int zstride, int slot0, int lane, int z, int S) {
-#pragma unroll
-  for (int u = 0; u < NS; ++u) g[u] = f32x4{0.f, 0.f, 0.f, 0.f};
-  for (int z0 = 0; z0 < S; z0 += ZB) {
-    f32x4 t[ZB][NS];
-#pragma unroll
-    for (int d = 0; d < ZB; ++d) {
-      const int zz = z0 + d;
-      if (zz < S && zz != z) {
-#pragma unroll
-        for (int u = 0; u < NS; ++u)
-          t[d][u] = __builtin_amdgcn_raw_buffer_load_b128(r, zz * zstride + ((slot0 + u) * 64 + lane) * 16, 0,
-                                                          kCoherent);
-      }
-    }
-#pragma unroll
-    for (int d = 0; d < ZB; ++d) {
-      const int zz = z0 + d;
-      if (zz < S) {
-#pragma unroll
-        for (int u = 0; u < NS; ++u) g[u] += zz == z ? own[u] : t[d][u];
-      }
-    }
-  }
-}
+struct EpiChangePartial : EpiPartial {};
 
 // --------------------------------------------------------------------------
 // Tiled fp32 product C[M][N] = sum_k A(m, k) B(k, n) on the bf16 matrix cores.
@@ -598,75 +508,16 @@ __global__ __launch_bounds__(tile_threads(BM)) void gemm_kernel(const float* __r
                  m0 + wm0 + i * 32 + 8 * (e >> 2) + 4 * h + (e & 3) < M;
     if (__syncthreads_or(odd)) fp32_tile<A_KM, B_NK, T::TM, T::TN>(A, lda, B, ldb, M, N, kb, ke, m0 + wm0, n0 + wn0, acc);
   }
-  if constexpr (std::is_same_v<Epi, EpiSplitUpdate>) {
-    // The block's partial (slot (i TN + j) 4 + q of a wave = registers 4 q
-    // .. 4 q + 3 of block (i, j)), its arrival, and in the last block of the
-    // tile the ordered sum of the splits and the update.
-    constexpr int kSlots = T::TM * T::TN * 4;
-    const int tile = tm * tiles_n + tn;
-    const int zstride = tiles_m * tiles_n * BM * BN * 4;
-    const __amdgpu_buffer_rsrc_t pr = partial_rsrc(epi.P + (size_t)tile * BM * BN + wave * kSlots * 256);
-    const int z = blockIdx.z;
-#pragma unroll
-    for (int i = 0; i < T::TM; ++i)
-#pragma unroll
-      for (int j = 0; j < T::TN; ++j)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-          __builtin_amdgcn_raw_buffer_store_b128(v, pr, z * zstride + (((i * T::TN + j) * 4 + q) * 64 + lane) * 16, 0,
-                                                 kCoherent);
-        }
-    if (!split_arrive(epi, tile)) return;
-    int nf = 0;
-#pragma unroll
-    for (int i = 0; i < T::TM; ++i)
-#pragma unroll
-      for (int j = 0; j < T::TN; ++j) {
-        const int n = n0 + wn0 + j * 32 + r, nc = min(n, N - 1);
-        // NS 4-row slots at a time (all four; the 1024-thread blocks have
-        // registers for two beside their accumulators)
-        constexpr int NS = BM == 256 ? 2 : 4;
-#pragma unroll
-        for (int q0 = 0; q0 < 4; q0 += NS) {
-          auto row = [&](int e) { return m0 + wm0 + i * 32 + 8 * (q0 + (e >> 2)) + 4 * h + (e & 3); };
-          float vo[4 * NS], wo[4 * NS];
-#pragma unroll
-          for (int e = 0; e < 4 * NS; ++e) {
-            const size_t idx = (size_t)min(row(e), M - 1) * epi.ldw + nc;
-            vo[e] = epi.V[idx];
-            wo[e] = epi.W[idx];
-          }
-          f32x4 own[NS], g[NS];
-#pragma unroll
-          for (int q = 0; q < NS; ++q)
-#pragma unroll
-            for (int e = 0; e < 4; ++e) own[q][e] = acc[i][j][4 * (q0 + q) + e];
-          ordered_split_sum<NS, (BM == 64 && BN == 64) ? 8 : 1>(g, own, pr, zstride, (i * T::TN + j) * 4 + q0, lane, z,
-                                                                 epi.splits);
-          if (n < N) {
-#pragma unroll
-            for (int e = 0; e < 4 * NS; ++e) {
-              if (row(e) < M) {
-                const size_t idx = (size_t)row(e) * epi.ldw + n;
-                const float v = momentum_step(checked_change(g[e >> 2][e & 3], epi.limit, nf), vo[e], epi.lr, epi.mom);
-                epi.V[idx] = v;
-                epi.W[idx] = wo[e] + v;
-              }
-            }
-          }
-        }
-      }
-    if (epi.limit > 0.f) add_faults(nf, epi.faults);
-  } else {
-    // Row epilogue of whole tiles of the sigmoid and hidden-delta products, 64
+  {
+    // Row epilogue of whole tiles of sigmoid, hidden-delta and partial sums, 64
     // rows (one column-sum group) at a time: the accumulators of those rows go
     // to LDS (the idle stage buffers, row stride BN + 8 floats: the two lane
     // halves of a register write land 32 banks apart), then each thread takes
     // 4 adjacent columns of every SL-th row as float4: one 16-byte load of the
     // operand and one 16-byte store per row instead of four 4-byte ones, every
     // wave instruction covering whole cache lines.
-    constexpr bool kRowEpi = std::is_same_v<Epi, EpiSigmoid> || std::is_same_v<Epi, EpiHiddenDelta>;
+    constexpr bool kPartial = std::is_base_of_v<EpiPartial, Epi>;
+    constexpr bool kRowEpi = std::is_same_v<Epi, EpiSigmoid> || std::is_same_v<Epi, EpiHiddenDelta> || kPartial;
     if constexpr (kRowEpi) {
       constexpr int RS = BN + 8, C4N = BN / 4, SL = NTH / C4N;   // row stride; float4 per row; row slices
       constexpr int RPT = 64 / SL;                               // rows per thread
@@ -676,6 +527,8 @@ __global__ __launch_bounds__(tile_threads(BM)) void gemm_kernel(const float* __r
       if constexpr (std::is_same_v<Epi, EpiHiddenDelta>)
         vec = vec && (epi.lda & 3) == 0 && (reinterpret_cast<uintptr_t>(epi.act) & 15) == 0;
       if (vec) {
+        float* out = epi.out;
+        if constexpr (kPartial) out += blockIdx.z * epi.split_stride;
         float* buf = reinterpret_cast<float*>(&lds[0][0]);
         const int c4 = tid % C4N, r0 = tid / C4N;
         const int n = n0 + 4 * c4;
@@ -713,10 +566,12 @@ __global__ __launch_bounds__(tile_threads(BM)) void gemm_kernel(const float* __r
             for (int q = 0; q < 4; ++q) {
               if constexpr (std::is_same_v<Epi, EpiSigmoid>)
                 v[q] = unit_sigma(a[q] + b4[q], epi.tab);
+              else if constexpr (kPartial)
+                v[q] = a[q];
               else
                 v[q] = a[q] * (pre[i][q] * (1.0f - pre[i][q]));
             }
-            *reinterpret_cast<f32x4*>(epi.out + (size_t)(mg + row) * epi.ldo + n) = v;
+            *reinterpret_cast<f32x4*>(out + (size_t)(mg + row) * epi.ldo + n) = v;
             if constexpr (Epi::kColSum) cs += v;
           }
           if constexpr (Epi::kColSum) {
@@ -846,12 +701,11 @@ hipError_t launch_tile(hipStream_t s, TileShape t, const float* A, int lda, cons
 // row block are added through LDS in K order, and the four waves of the row
 // block share its epilogue (RB = 2 for epilogues with 64-row column sums).
 //
-// With EpiSplitUpdate the kernel is a split-K change product (section
+// With EpiChangePartial the kernel is a split-K change product (section
 // 6.2.1, the batch-summed change of one layer's weights when the batch is
 // long and the layer small): A is stored k-major (A[k][m], the activations),
 // the block covers K range [z k_chunk, (z + 1) k_chunk) of split z and
-// stores its partial sums; the last block of each tile adds them in split
-// order and applies the update (EpiSplitUpdate).  Blocks are ordered split-major and handed to
+// stores its partial sums.  Blocks are ordered split-major and handed to
 // the XCDs in contiguous ranges, so each XCD reads one K range of both
 // operands.
 //
@@ -882,7 +736,7 @@ __device__ __forceinline__ void skinny_body(int bid, int nblocks, float (&part)[
                                             const float* __restrict__ A, int lda, const float* __restrict__ B,
                                             int ldb, int M, int N, int K, int k_chunk, const Epi& epi,
                                             const CtxInput& ctx) {
-  constexpr bool SPLIT = std::is_same_v<Epi, EpiSplitUpdate>;
+  constexpr bool SPLIT = std::is_same_v<Epi, EpiChangePartial>;
   static_assert(!Epi::kFaults || SPLIT, "unsplit update epilogues take gemm_kernel");
   static_assert(!Epi::kColSum || RB == 2, "64-row column sums need RB = 2");
   static_assert(!A_KM || (SPLIT && !AVEC && !CTX), "k-major A is the change product's");
@@ -1032,43 +886,13 @@ __device__ __forceinline__ void skinny_body(int bid, int nblocks, float (&part)[
   for (int e = 0; e < 16; ++e) part[kg][rb][e][lane] = acc[e];
   __syncthreads();
   if constexpr (SPLIT) {
-    // One 4-float slot per thread (slot = wave): rows 8 kg + 4 h + q of row
-    // block rb, column n.  Then the arrival, and in the last block of the
-    // tile the ordered sum of the splits and the update.
-    f32x4 own[1], g[1];
+    // rows 8 kg + 4 h + q of row block rb, column n, of split z
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      const int e = 4 * kg + q;
-      own[0][q] = ((part[0][rb][e][lane] + part[1][rb][e][lane]) + part[2][rb][e][lane]) + part[3][rb][e][lane];
+      const int e = 4 * kg + q, mm = m0 + rb * 32 + 8 * kg + 4 * h + q;
+      const float v = ((part[0][rb][e][lane] + part[1][rb][e][lane]) + part[2][rb][e][lane]) + part[3][rb][e][lane];
+      if (n < N && mm < M) epi.out[z * epi.split_stride + (size_t)mm * epi.ldo + n] = v;
     }
-    const int tile = tm * tiles_n + tn;
-    const int zstride = tiles_m * tiles_n * 32 * RB * 32 * 4;
-    const __amdgpu_buffer_rsrc_t pr = partial_rsrc(epi.P + (size_t)tile * 32 * RB * 32);
-    __builtin_amdgcn_raw_buffer_store_b128(own[0], pr, z * zstride + (wave * 64 + lane) * 16, 0, kCoherent);
-    if (!split_arrive(epi, tile)) return;
-    const int nc = min(n, N - 1);
-    float vo[4], wo[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const size_t idx = (size_t)min(m0 + rb * 32 + 8 * kg + 4 * h + q, M - 1) * epi.ldw + nc;
-      vo[q] = epi.V[idx];
-      wo[q] = epi.W[idx];
-    }
-    ordered_split_sum<1>(g, own, pr, zstride, wave, lane, z, epi.splits);
-    int nf = 0;
-    if (n < N) {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const int mm = m0 + rb * 32 + 8 * kg + 4 * h + q;
-        if (mm < M) {
-          const size_t idx = (size_t)mm * epi.ldw + n;
-          const float v = momentum_step(checked_change(g[0][q], epi.limit, nf), vo[q], epi.lr, epi.mom);
-          epi.V[idx] = v;
-          epi.W[idx] = wo[q] + v;
-        }
-      }
-    }
-    if (epi.limit > 0.f) add_faults(nf, epi.faults);
   } else {
     float sse = 0.f, csum = 0.f;
     if (n < N) {
@@ -1240,42 +1064,50 @@ __global__ __launch_bounds__(kFin) void output_finish_kernel(const float* __rest
   }
 }
 
-// Bias-row changes of several layers in one launch: column sums of each
-// layer's D over its `rows` rows, then the update.  Blocks [block0, next
-// job's block0) take the job's 64-column strips.  Block = 1024 threads = 16
-// waves; lane = column within a strip; wave w sums its contiguous share of
-// the rows in order, then the 16 partial sums are added in wave order.
+// The end of an update: the bias-row changes of several layers, and the split
+// change products' sums, each with its momentum step.  Blocks of 1024 threads
+// = 16 waves.
+//   Bias rows: blocks [block0, next job's block0) take a job's 64-column
+// strips; lane = column within a strip; wave w sums its contiguous share of
+// the rows of D in order, then the 16 partial sums are added in wave order.
+//   Changes: a thread takes four adjacent columns of one row and adds the
+// splits in split order, up to eight of them in flight.  HBM-bound, 4 (splits +
+// 4) bytes per weight; this pass of the whole chip costs less than letting the
+// last block of each output tile add its tile's partials, which leaves the
+// other CUs idle (the 512-2048-2048-2048-64 net's changes at 8192 rows: 992
+// us an update that way, 845 this way, this launch 22 us of it three times).
 constexpr int kBiasWaves = 16;
-__global__ __launch_bounds__(64 * kBiasWaves) void bias_update_kernel(BiasJobs jobs, float lr, float mom,
-                                                                       float limit, unsigned long long* faults) {
+constexpr int kFinish = 64 * kBiasWaves;
+__global__ __launch_bounds__(kFinish) void update_finish_kernel(FinishJobs jobs, float lr, float mom, float limit,
+                                                                unsigned long long* faults) {
   __shared__ float part[kBiasWaves][64];
-  int q = 0;
-  while (q + 1 < jobs.n && (int)blockIdx.x >= jobs.j[q + 1].block0) ++q;
-  const float* __restrict__ D = jobs.j[q].D;
-  float* Wb = jobs.j[q].Wb;
-  float* Vb = jobs.j[q].Vb;
-  const int ldd = jobs.j[q].ldd, rows = jobs.j[q].rows, N = jobs.j[q].N;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int n = ((int)blockIdx.x - jobs.j[q].block0) * 64 + lane;
-  const int r0 = (int)((int64_t)rows * wave / kBiasWaves), r1 = (int)((int64_t)rows * (wave + 1) / kBiasWaves);
-  float s = 0.f;
-  if (n < N) {
-    int k = r0;
-    for (; k + 4 <= r1; k += 4) {
-      const float a0 = D[(size_t)k * ldd + n], a1 = D[(size_t)(k + 1) * ldd + n];
-      const float a2 = D[(size_t)(k + 2) * ldd + n], a3 = D[(size_t)(k + 3) * ldd + n];
-      s += a0;
-      s += a1;
-      s += a2;
-      s += a3;
-    }
-    for (; k < r1; ++k) s += D[(size_t)k * ldd + n];
-  }
-  part[wave][lane] = s;
-  __syncthreads();
-  if (wave == 0) {
-    int nf = 0;
+  int nf = 0;
+  if ((int)blockIdx.x < jobs.change_block0) {
+    int q = 0;
+    while (q + 1 < jobs.n_bias && (int)blockIdx.x >= jobs.bias[q + 1].block0) ++q;
+    const float* __restrict__ D = jobs.bias[q].D;
+    float* Wb = jobs.bias[q].Wb;
+    float* Vb = jobs.bias[q].Vb;
+    const int ldd = jobs.bias[q].ldd, rows = jobs.bias[q].rows, N = jobs.bias[q].N;
+    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int n = ((int)blockIdx.x - jobs.bias[q].block0) * 64 + lane;
+    const int r0 = (int)((int64_t)rows * wave / kBiasWaves), r1 = (int)((int64_t)rows * (wave + 1) / kBiasWaves);
+    float s = 0.f;
     if (n < N) {
+      int k = r0;
+      for (; k + 4 <= r1; k += 4) {
+        const float a0 = D[(size_t)k * ldd + n], a1 = D[(size_t)(k + 1) * ldd + n];
+        const float a2 = D[(size_t)(k + 2) * ldd + n], a3 = D[(size_t)(k + 3) * ldd + n];
+        s += a0;
+        s += a1;
+        s += a2;
+        s += a3;
+      }
+      for (; k < r1; ++k) s += D[(size_t)k * ldd + n];
+    }
+    part[wave][lane] = s;
+    __syncthreads();
+    if (wave == 0 && n < N) {
       float g = 0.f;
       for (int w = 0; w < kBiasWaves; ++w) g += part[w][lane];
       g = checked_change(g, limit, nf);
@@ -1283,8 +1115,38 @@ __global__ __launch_bounds__(64 * kBiasWaves) void bias_update_kernel(BiasJobs j
       Vb[n] = v;
       Wb[n] = Wb[n] + v;
     }
-    if (limit > 0.f) add_faults(nf, faults);
+  } else {
+    int q = 0;
+    while (q + 1 < jobs.n_change && (int)blockIdx.x >= jobs.change[q + 1].block0) ++q;
+    const int ldp = jobs.change[q].ldp, N = jobs.change[q].N, splits = jobs.change[q].splits;
+    const uint32_t f = ((uint32_t)blockIdx.x - jobs.change[q].block0) * kFinish + threadIdx.x, per_row = ldp / 4;
+    const uint32_t m = f / per_row, n = (f - m * per_row) * 4;
+    if (m < (uint32_t)jobs.change[q].M) {
+      const float* __restrict__ P = jobs.change[q].P + (size_t)m * ldp + n;
+      const size_t stride = jobs.change[q].stride;
+      f32x4* pv = reinterpret_cast<f32x4*>(jobs.change[q].V + (size_t)m * jobs.change[q].ldw + n);
+      f32x4* pw = reinterpret_cast<f32x4*>(jobs.change[q].W + (size_t)m * jobs.change[q].ldw + n);
+      f32x4 v = *pv, w = *pw, g = {0.f, 0.f, 0.f, 0.f};
+      for (int z0 = 0; z0 < splits; z0 += 8) {
+        f32x4 t[8];
+#pragma unroll
+        for (int d = 0; d < 8; ++d)
+          if (z0 + d < splits) t[d] = *reinterpret_cast<const f32x4*>(P + (z0 + d) * stride);
+#pragma unroll
+        for (int d = 0; d < 8; ++d)
+          if (z0 + d < splits) g += t[d];
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        if ((int)n + e >= N) continue;          // a row's padding stays as it is
+        v[e] = momentum_step(checked_change(g[e], limit, nf), v[e], lr, mom);
+        w[e] += v[e];
+      }
+      *pv = v;
+      *pw = w;
+    }
   }
+  if (limit > 0.f) add_faults(nf, faults);
 }
 
 // One-hot first layer forward.  LP lanes per (pattern, strip of 4 LP columns),
@@ -1501,13 +1363,6 @@ __global__ __launch_bounds__(kThreads) void copy_flat_kernel(FlatJobs jobs, int6
   }
 }
 
-// Zero fill of n ints (counters that must start at zero, in work a caller
-// may capture into a graph, where a memset node is avoided).
-__global__ __launch_bounds__(kThreads) void zero_ints_kernel(int* p, int n) {
-  const int i = blockIdx.x * kThreads + threadIdx.x;
-  if (i < n) p[i] = 0;
-}
-
 // Fixed-order sum of n doubles by one block of 1024 threads: thread t adds
 // elements t, t + 1024, ... (loads issued eight at a time), then a tree.
 constexpr int kRed = 1024;
@@ -1519,17 +1374,17 @@ __global__ __launch_bounds__(kRed) void sse_reduce_kernel(const double* __restri
 // How an M x N product summed over K runs: its tile and the number of K
 // ranges (splits) it is cut into, each a multiple of the stage.
 //
-// The rule compares estimated times.  A stage (16 k) of q blocks per CU takes
-// about (measured at K = 1024, one to sixteen blocks per CU; microseconds)
+// The rule compares estimated times.  A launch starts and ends in about 5 us,
+// and a stage (16 k) of q blocks per CU takes about (measured at K = 1024, one
+// to sixteen blocks per CU; microseconds)
 //   256 x 256:  1.0 + 1.75 q      128 x 128:  0.10 + 0.84 q      64 x 64:  0.30 + 0.25 q
 // (the larger tiles move less data per product, the smaller ones leave less of
-// the chip idle), and splitting costs what `split_us` says.
+// the chip idle).  What a number of splits costs besides, the caller says.
 struct Plan {
   TileShape tile;
   int splits;
   int chunk;        // K range of a split
-  int tiles() const { return tiles_of(M, N, tile.m, tile.n); }
-  int M, N;
+  double us;        // the estimate
 };
 
 double stage_us(int edge, int blocks) {
@@ -1537,22 +1392,20 @@ double stage_us(int edge, int blocks) {
   return edge == 256 ? 1.0 + 1.75 * q : edge == 128 ? 0.10 + 0.84 * q : 0.30 + 0.25 * q;
 }
 
-// split_us(edge, tiles, splits): microseconds that `splits` > 1 ranges cost
+constexpr int kMinSplitK = 96;   // shortest K range of a split
+
 template <class F>
 Plan plan_product(int M, int N, int K, int max_splits, F&& split_us) {
-  Plan best{{64, 64}, 1, K, M, N};
-  double best_us = 1e30;
+  Plan best{{64, 64}, 1, K, 1e30};
+  const int stages = (K + kStageK - 1) / kStageK;
   for (int edge : {256, 128, 64}) {
     const int tiles = tiles_of(M, N, edge, edge);
-    for (int s = 1; s <= max_splits && (s == 1 || (K / s >= 256 && (long)tiles * s <= 4 * kCUs &&
+    for (int s = 1; s <= max_splits && (s == 1 || (K / s >= kMinSplitK && (long)tiles * s <= 4 * kCUs &&
                                                    (size_t)tiles * s * edge * edge <= kMaxSplitFloats));
          ++s) {
-      const int stages = (K + kStageK - 1) / kStageK, per = (stages + s - 1) / s;
-      const double us = per * stage_us(edge, tiles * s) + (s > 1 ? split_us(edge, tiles, s) : 0.0);
-      if (us < best_us) {
-        best_us = us;
-        best = {{edge, edge}, s, per * kStageK, M, N};
-      }
+      const int per = (stages + s - 1) / s;
+      const double us = 5.0 + per * stage_us(edge, tiles * s) + split_us(s);
+      if (us < best.us) best = {{edge, edge}, s, per * kStageK, us};
     }
   }
   // every split gets a part of K
@@ -1562,13 +1415,13 @@ Plan plan_product(int M, int N, int K, int max_splits, F&& split_us) {
 }
 
 TileShape tile_shape(int M, int N, int K) {
-  return plan_product(M, N, K, 1, [](int, int, int) { return 0.0; }).tile;
+  return plan_product(M, N, K, 1, [](int) { return 0.0; }).tile;
 }
 
 // Output layer: its split partials cross memory once more, and a launch
 // (output_finish_kernel) adds them.
 Plan output_plan(int M, int N, int K) {
-  return plan_product(M, N, K, 16, [&](int, int, int s) { return 6.0 + (double)s * M * N * 8.0 / 4e6; });
+  return plan_product(M, N, K, 16, [&](int s) { return s > 1 ? 6.0 + (double)s * M * N * 8.0 / 4e6 : 0.0; });
 }
 
 int choose_output_splits(int M, int N, int K) { return use_skinny(M, N, K) ? 1 : output_plan(M, N, K).splits; }
@@ -1588,7 +1441,8 @@ int colsum_rows(int M) { return (M + 63) / 64; }
 int output_delta_blocks(int M, int N, int K) {
   if (use_skinny(M, N, K)) return ((M + 63) / 64) * ((N + 31) / 32);
   if (choose_output_splits(M, N, K) > 1) return ((M + 127) / 128) * ((N + 63) / 64);
-  return output_plan(M, N, K).tiles();
+  const TileShape t = output_plan(M, N, K).tile;
+  return tiles_of(M, N, t.m, t.n);
 }
 
 size_t output_delta_workspace(int M, int N, int K) {
@@ -1670,7 +1524,7 @@ hipError_t forward_output_delta(hipStream_t s, const float* A, int lda, const fl
     return launch_tile<false, false>(s, output_plan(M, N, K).tile, A, lda, W, ldw, M, N, K, 1, K, e);
   }
   const int ldp = (N + 3) / 4 * 4;
-  EpiPartial e{ws, ldp, (size_t)M * ldp};
+  const EpiPartial e{ws, ldp, (size_t)M * ldp};
   const Plan pl = output_plan(M, N, K);
   return launch_tile<false, false>(s, pl.tile, A, lda, W, ldw, M, N, K, sp, pl.chunk, e);
 }
@@ -1693,48 +1547,33 @@ hipError_t backward_layer(hipStream_t s, const float* D, int ldd, const float* W
   return launch_tile<false, true>(s, tile_shape(M, N, K), D, ldd, W, ldw, M, N, K, 1, K, e);
 }
 
-// The change product of a layer: few output tiles and a long batch take the
-// split-K skinny kernel (64 x 32 tiles), with the largest K chunk of 1024,
-// 512, 256 or 128 that still gives kSkinnyChangeBlocks blocks (one per CU:
-// every block pays the arrival's round trips once); the others
-// take gemm_kernel, split over K when the batch is long (choose_splits).
-// Split products apply the update in the last block of each tile
-// (EpiSplitUpdate); the others in every block's epilogue (EpiUpdate).
-constexpr int kSkinnyChangeBlocks = 256;
+// The change product of a layer, by the shorter estimate: the skinny kernel on
+// at most 128 tiles of 64 x 32, split over K to about one block per CU (4 us
+// and 13.5 ns per k of a split's range; 300 x 300 over 500 rows: 8.7 us with the
+// finishing launch against 30.9 for unsplit 64 x 64 tiles), or gemm_kernel.
+// Split products, and the skinny kernel's always, leave partials for
+// update_finish_kernel (which costs each split one way through memory and back); the
+// others apply the update in every block's epilogue (EpiUpdate, 4-byte
+// accesses to the weights: 5 us).
 struct ChangePlan {
   bool skinny;
+  bool partial;     // leaves partials
   int splits;
   int chunk;
-  int tiles;        // output tiles
-  int tile_elems;   // floats per output tile
-  TileShape tile{0, 0};  // gemm_kernel's
+  TileShape tile;   // gemm_kernel's
 };
 
 ChangePlan change_plan(int M, int N, int K) {
-  const int tiles64 = tiles_of(M, N, 64, 64);
-  // long K over 16-127 output tiles of 64 x 64: those tiles split over K on
-  // about one block per CU
-  if (K >= 4096 && tiles64 >= 16 && tiles64 < 128) {
-    const int stages = (K + kStageK - 1) / kStageK, want = std::min((kCUs + tiles64 - 1) / tiles64, K / 256);
-    const int chunk = (stages + want - 1) / want * kStageK;
-    return {false, (K + chunk - 1) / chunk, chunk, tiles64, 64 * 64, {64, 64}};
+  auto split_us = [&](int s) { return 3.0 + (double)s * M * N * 8.0 / 4e6; };
+  const Plan pl = plan_product(M, N, K, 64, [&](int s) { return s > 1 ? split_us(s) : 5.0; });
+  const int tiles = tiles_of(M, N, 64, 32);
+  if (tiles <= kCUs / 2) {
+    const int want = std::max(1, std::min(kCUs / tiles, K / 128));
+    const int chunk = ((K + want - 1) / want + 31) / 32 * 32, splits = std::max(1, (K + chunk - 1) / chunk);
+    if (4.0 + 0.0135 * chunk + split_us(splits) < pl.us) return {true, true, splits, chunk, {0, 0}};
   }
-  if (K >= 1024 && tiles64 < 128) {
-    const int tiles = ((M + 63) / 64) * ((N + 31) / 32);
-    int chunk = 1024;
-    while (chunk > 128 && (long)tiles * ((K + chunk - 1) / chunk) < kSkinnyChangeBlocks) chunk /= 2;
-    const int sp = (K + chunk - 1) / chunk;
-    if (sp >= 2) return {true, sp, chunk, tiles, 64 * 32};
-  }
-  // a split costs its partials' way through memory and the last block's sum
-  const Plan pl = plan_product(M, N, K, 64, [](int edge, int tiles, int s) {
-    const double kb = edge * edge * 4e-3;
-    return 4.0 + (s + 3.0) * kb * 0.012 + (double)tiles * s * kb * 1e-3 * 0.4;
-  });
-  return {false, pl.splits, pl.chunk, pl.tiles(), pl.tile.m * pl.tile.n, pl.tile};
+  return {false, pl.splits > 1, pl.splits, pl.chunk, pl.tile};
 }
-
-int change_splits(int M, int N, int K) { return change_plan(M, N, K).splits; }
 
 // What a fixed scratch counts for the split partials of an M x N change (or,
 // output, of the output layer's product) summed over K: 512 tiles of
@@ -1767,47 +1606,53 @@ int scratch_error_blocks(int M, int N, int K) {
   return tiles_of(M, N, bm, bm == 128 && N <= 64 ? 64 : bm);
 }
 
-size_t change_update_workspace(int M, int N, int K) {
+size_t change_partial_floats(int M, int N, int K) {
   const ChangePlan pl = change_plan(M, N, K);
-  return pl.splits > 1 ? (size_t)pl.splits * pl.tiles * pl.tile_elems : 0;
+  return pl.partial ? (size_t)pl.splits * M * ((N + 3) / 4 * 4) : 0;
 }
 
-int change_arrivals(int M, int N, int K) {
-  const ChangePlan pl = change_plan(M, N, K);
-  return pl.splits > 1 ? pl.tiles : 0;
-}
-
-hipError_t change_update(hipStream_t s, const float* A, int lda, const float* D, int ldd, int M, int N, int K,
-                         float* W, float* V, int ldw, float lr, float mom, float* ws, int* arrivals, float limit,
-                         unsigned long long* faults) {
+hipError_t change_product(hipStream_t s, const float* A, int lda, const float* D, int ldd, int M, int N, int K,
+                          float* W, float* V, int ldw, float lr, float mom, float limit, unsigned long long* faults,
+                          float* partials, ChangeJob* job) {
   if (M <= 0 || N <= 0) return hipSuccess;
   const ChangePlan pl = change_plan(M, N, K);
-  if (pl.splits <= 1) {
+  if (!pl.partial) {
     EpiUpdate e{W, V, ldw, lr, mom, limit, faults};
     return launch_tile<true, false>(s, pl.tile, A, lda, D, ldd, M, N, K, 1, K, e);
   }
-  if (!arrivals || !ws || pl.tiles > kMaxArrivals) return hipErrorInvalidValue;
-  EpiSplitUpdate e{ws, W, V, ldw, lr, mom, limit, faults, arrivals, pl.splits};
+  if (!partials || !job) return hipErrorInvalidValue;
+  const int ldp = (N + 3) / 4 * 4;
+  *job = {partials, W, V, (size_t)M * ldp, pl.splits, M, N, ldp, ldw, 0};
+  EpiChangePartial e;
+  e.out = partials;
+  e.ldo = ldp;
+  e.split_stride = (size_t)M * ldp;
   if (pl.skinny)
-    return launch_kernel(skinny_kernel<2, true, false, false, false, false, EpiSplitUpdate>, pl.tiles * pl.splits, 512,
-                         0, s, A, lda, D, ldd, M, N, K, pl.chunk, e, CtxInput{});
+    return launch_kernel(skinny_kernel<2, true, false, false, false, false, EpiChangePartial>,
+                         tiles_of(M, N, 64, 32) * pl.splits, 512, 0, s, A, lda, D, ldd, M, N, K, pl.chunk, e,
+                         CtxInput{});
   return launch_tile<true, false>(s, pl.tile, A, lda, D, ldd, M, N, K, pl.splits, pl.chunk, e);
 }
 
-hipError_t bias_update(hipStream_t s, const BiasJob* jobs, int n, float lr, float mom, float limit,
-                       unsigned long long* faults) {
-  for (int j0 = 0; j0 < n; j0 += kMaxBiasJobs) {
-    BiasJobs b{};
+hipError_t finish_update(hipStream_t s, const BiasJob* bias, int n_bias, const ChangeJob* change, int n_change,
+                         float lr, float mom, float limit, unsigned long long* faults) {
+  while (n_bias > 0 || n_change > 0) {
+    FinishJobs b{};
     int blocks = 0;
-    for (int j = j0; j < n && j < j0 + kMaxBiasJobs; ++j) {
-      if (jobs[j].N <= 0) continue;
-      b.j[b.n] = jobs[j];
-      b.j[b.n].block0 = blocks;
-      blocks += (jobs[j].N + 63) / 64;
-      ++b.n;
+    for (; n_bias > 0 && b.n_bias < kMaxFinishJobs; ++bias, --n_bias) {
+      if (bias->N <= 0) continue;
+      b.bias[b.n_bias] = *bias;
+      b.bias[b.n_bias++].block0 = blocks;
+      blocks += (bias->N + 63) / 64;
+    }
+    b.change_block0 = blocks;
+    for (; n_change > 0 && b.n_change < kMaxFinishJobs; ++change, --n_change) {
+      b.change[b.n_change] = *change;
+      b.change[b.n_change++].block0 = blocks;
+      blocks += (int)(((int64_t)change->M * (change->ldp / 4) + kFinish - 1) / kFinish);
     }
     if (blocks == 0) continue;
-    const hipError_t e = launch_kernel(bias_update_kernel, blocks, 64 * kBiasWaves, 0, s, b, lr, mom, limit, faults);
+    const hipError_t e = launch_kernel(update_finish_kernel, blocks, kFinish, 0, s, b, lr, mom, limit, faults);
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
@@ -1865,11 +1710,6 @@ hipError_t copy_flat(hipStream_t s, const FlatLayer* layers, int n_layers, int64
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
-}
-
-hipError_t zero_ints(hipStream_t s, int* p, int n) {
-  if (n <= 0) return hipSuccess;
-  return launch_kernel(zero_ints_kernel, (n + kThreads - 1) / kThreads, kThreads, 0, s, p, n);
 }
 
 }  // namespace bpk

@@ -46,7 +46,6 @@ struct bp_net {
   size_t fwd_cap = 0;
   float* splitk = nullptr;
   size_t splitk_cap = 0;
-  int* arrivals = nullptr;            // split-K arrival counters (bpk::kMaxArrivals), zero between launches
   double* sse_part = nullptr;
   size_t sse_cap = 0;
   double* sse_dev = nullptr;
@@ -130,7 +129,8 @@ struct bp_net {
 // scratch_split_floats and scratch_error_blocks do, is at most kScratchBytes;
 // the array also has room for the largest partials a plan may use instead.
 constexpr size_t kScratchBytes = (size_t)64 << 20;
-static __device__ __align__(256) float scratch[kScratchBytes / sizeof(float) + bpk::kMaxSplitFloats];
+constexpr size_t kPendingFloats = (size_t)8 << 20;   // see splitk_floats
+static __device__ __align__(256) float scratch[kScratchBytes / sizeof(float) + bpk::kMaxSplitFloats + kPendingFloats];
 
 namespace {
 
@@ -252,13 +252,20 @@ void free_workspace(bp_net* net) {
 
 // Floats of split-K workspace one forward pass over `fwd_rows` patterns and
 // the change products over `chg_rows` patterns need (used one at a time).
+// The changes' partials share it until finish_update adds them: all of them
+// where that is no more than kPendingFloats beyond the largest.
 // The output layer's need is not monotonic in its row count (fewer rows,
 // more splits), so callers ask for every row count they will use.
 size_t splitk_floats(const bp_net* net, int64_t fwd_rows, int64_t chg_rows) {
-  size_t sk = fwd_rows > 0 ? bpk::output_delta_workspace((int)fwd_rows, net->n[net->L], net->n[net->L - 1]) : 0;
-  for (int l = 0; l < net->L && chg_rows > 0; ++l)
-    sk = std::max(sk, bpk::change_update_workspace(net->n[l], net->n[l + 1], (int)chg_rows));
-  return sk;
+  size_t largest = 0, sum = 0;
+  for (int l = 0; l < net->L && chg_rows > 0; ++l) {
+    const size_t n = bpk::change_partial_floats(net->n[l], net->n[l + 1], (int)chg_rows);
+    largest = std::max(largest, n);
+    sum += n;
+  }
+  const size_t out =
+      fwd_rows > 0 ? bpk::output_delta_workspace((int)fwd_rows, net->n[net->L], net->n[net->L - 1]) : 0;
+  return std::max(out, std::min(sum, largest + kPendingFloats));
 }
 
 // Workspace for batches of up to `rows` patterns, `top_csum` column-sum rows
@@ -473,12 +480,24 @@ int run_small(bp_net* net, const BatchInput& in, int rows, const float* T, doubl
 }
 
 // Backward pass and update of one batch whose deltas of the output layer are
-// in del[L].  The bias rows, which no delta or change product reads, are
-// updated together in one launch after the last change product.
+// in del[L].  What the products leave to be added and applied (split changes'
+// partials, and the bias rows, which no delta or change product reads) is
+// finished together after the last change product, or before it when the
+// partials' workspace is full.
 int run_backward_update(bp_net* net, const BatchInput& in, int rows, float lr, float mom, int top_csum = 0) {
   hipStream_t s = net->stream;
-  bpk::BiasJob bias[bpk::kMaxBiasJobs];
-  int nb = 0;
+  bpk::BiasJob bias[bpk::kMaxFinishJobs];
+  bpk::ChangeJob change[bpk::kMaxFinishJobs];
+  int nb = 0, nc = 0;
+  size_t used = 0;                    // floats of partials pending
+  auto finish = [&]() {
+    if (nb + nc > 0)
+      BP_LAUNCH(net, BP_K_BIAS,
+                bpk::finish_update(s, bias, nb, change, nc, lr, mom, net->fault_limit, net->faults));
+    nb = nc = 0;
+    used = 0;
+    return (int)BP_OK;
+  };
   for (int l = net->L - 1; l >= 0; --l) {
     // Hidden deltas of layer l use W_l before its update.
     if (l >= 1)
@@ -497,21 +516,26 @@ int run_backward_update(bp_net* net, const BatchInput& in, int rows, float lr, f
     } else {
       const float* A = (l == 0) ? in.x : net->act[l];
       const int ldA = (l == 0) ? ldx_of(net, in) : net->lda[l];
-      const bool split = bpk::change_splits(net->n[l], net->n[l + 1], rows) > 1;
-      BP_LAUNCH(net, split ? BP_K_SPLITK : BP_K_CHANGE,
-                bpk::change_update(s, A, ldA, net->del[l + 1], net->lda[l + 1], net->n[l], net->n[l + 1], rows,
-                                   wl(net, l), vl(net, l), net->ldw[l], lr, mom, net->splitk, net->arrivals,
-                                   net->fault_limit, net->faults));
+      const size_t need = bpk::change_partial_floats(net->n[l], net->n[l + 1], rows);
+      if (used + need > net->splitk_cap || nc == bpk::kMaxFinishJobs) {
+        const int rc = finish();
+        if (rc) return rc;
+      }
+      BP_LAUNCH(net, need > 0 ? BP_K_SPLITK : BP_K_CHANGE,
+                bpk::change_product(s, A, ldA, net->del[l + 1], net->lda[l + 1], net->n[l], net->n[l + 1], rows,
+                                    wl(net, l), vl(net, l), net->ldw[l], lr, mom, net->fault_limit, net->faults,
+                                    net->splitk + used, &change[nc]));
+      if (need > 0) ++nc;
+      used += need;
     }
     bias[nb++] = {net->csum[l + 1], wbias(net, l), vbias(net, l), net->lda[l + 1],
                   (l + 1 == net->L && top_csum > 0) ? top_csum : bpk::colsum_rows(rows), net->n[l + 1], 0};
-    if (nb == bpk::kMaxBiasJobs) {
-      BP_LAUNCH(net, BP_K_BIAS, bpk::bias_update(s, bias, nb, lr, mom, net->fault_limit, net->faults));
-      nb = 0;
+    if (nb == bpk::kMaxFinishJobs) {
+      const int rc = finish();
+      if (rc) return rc;
     }
   }
-  if (nb > 0) BP_LAUNCH(net, BP_K_BIAS, bpk::bias_update(s, bias, nb, lr, mom, net->fault_limit, net->faults));
-  return BP_OK;
+  return finish();
 }
 
 // The launches of one training call: every batch, then the error reduction
@@ -658,7 +682,7 @@ int train_noalloc(bp_net* net, const BatchInput& in, const float* targets, int64
   const size_t n_sse = (size_t)sse_blocks(net, in, (int)rows_max) * (size_t)(nb - 1) +
                        (size_t)sse_blocks(net, in, last_rows);
   // layout, each piece on a 256-byte boundary: act[1..L-1], del[1..L],
-  // csum[1..L], arrival counters, error partials, error sum, split partials
+  // csum[1..L], error partials, error sum, split partials
   size_t off = 0;
   auto take = [&](size_t floats) {
     const size_t o = off;
@@ -672,7 +696,7 @@ int train_noalloc(bp_net* net, const BatchInput& in, const float* targets, int64
     oc[l] = take((size_t)bpk::colsum_rows((int)rows_max) * net->lda[l]);
   }
   // what decides whether the call is taken counts partials by a measure of
-  // their own (scratch_split_floats, scratch_error_blocks)
+  // their own (scratch_split_floats, scratch_error_blocks), and 512 words more
   auto padded = [](size_t floats) { return (floats + 63) / 64 * 64; };
   size_t counted = 0, counted_sse = 0;
   for (const int64_t rows : {rows_max, (int64_t)last_rows}) {
@@ -684,8 +708,7 @@ int train_noalloc(bp_net* net, const BatchInput& in, const float* targets, int64
     return (size_t)bpk::scratch_error_blocks((int)rows, net->n[net->L], net->n[net->L - 1]);
   };
   counted_sse = error_blocks(rows_max) * (size_t)(nb - 1) + error_blocks(last_rows);
-  counted = off + padded(counted) + padded(bpk::kMaxArrivals) + padded(2 * counted_sse) + padded(2);
-  const size_t oarr = take(bpk::kMaxArrivals);
+  counted = off + padded(counted) + padded(512) + padded(2 * counted_sse) + padded(2);
   const size_t osp = take(2 * n_sse);
   const size_t osd = take(2);
   const size_t osk = take(sk);
@@ -700,7 +723,7 @@ int train_noalloc(bp_net* net, const BatchInput& in, const float* targets, int64
   // swap the views in, run, swap back
   std::vector<float*> act = net->act, del = net->del, csum = net->csum;
   float* splitk = net->splitk;
-  int* arrivals = net->arrivals;
+  const size_t splitk_cap = net->splitk_cap;
   double* sse_part = net->sse_part;
   double* sse_dev = net->sse_dev;
   const bool prof = net->prof;
@@ -710,21 +733,17 @@ int train_noalloc(bp_net* net, const BatchInput& in, const float* targets, int64
     net->csum[l] = base + oc[l];
   }
   net->splitk = base + osk;
-  net->arrivals = reinterpret_cast<int*>(base + oarr);
+  net->splitk_cap = sk;
   net->sse_part = reinterpret_cast<double*>(base + osp);
   net->sse_dev = reinterpret_cast<double*>(base + osd);
   net->prof = false;
-  // the counters start at zero (every finished launch leaves them so; an
-  // earlier call that failed part way might not have)
-  const hipError_t ez = bpk::zero_ints(net->stream, net->arrivals, bpk::kMaxArrivals);
-  int rc = ez == hipSuccess ? BP_OK : hip_fail(net, ez, "bp_train_batches_noalloc: counter reset");
-  if (rc == BP_OK) rc = train_launches(net, in, targets, n, batch, lr, mom);
+  int rc = train_launches(net, in, targets, n, batch, lr, mom);
   double* sum = net->sse_dev;
   net->act = act;
   net->del = del;
   net->csum = csum;
   net->splitk = splitk;
-  net->arrivals = arrivals;
+  net->splitk_cap = splitk_cap;
   net->sse_part = sse_part;
   net->sse_dev = sse_dev;
   net->prof = prof;
@@ -1048,8 +1067,6 @@ int bp_create(const int32_t* layer_sizes, int32_t n_layers, bp_net** out) {
   if (e == hipSuccess) e = hipMalloc(&net->V, sizeof(float) * net->wtotal);
   if (e == hipSuccess) e = hipMemset(net->W, 0, sizeof(float) * net->wtotal);
   if (e == hipSuccess) e = hipMemset(net->V, 0, sizeof(float) * net->wtotal);
-  if (e == hipSuccess) e = hipMalloc(&net->arrivals, sizeof(int) * bpk::kMaxArrivals);
-  if (e == hipSuccess) e = hipMemset(net->arrivals, 0, sizeof(int) * bpk::kMaxArrivals);
   if (e == hipSuccess) e = hipHostMalloc(reinterpret_cast<void**>(&net->host_sse), sizeof(double), hipHostMallocDefault);
   if (e == hipSuccess) (void)scratch_on(net->device, &e);   // this device's scratch address, once
   if (e != hipSuccess) {
@@ -1057,7 +1074,6 @@ int bp_create(const int32_t* layer_sizes, int32_t n_layers, bp_net** out) {
     const int code = e == hipErrorOutOfMemory ? BP_ENOMEM : BP_EDEVICE;
     free_ptr(net->W);
     free_ptr(net->V);
-    free_ptr(net->arrivals);
     if (net->host_sse) (void)hipHostFree(net->host_sse);
     delete net;
     return code;
@@ -1083,7 +1099,6 @@ void bp_destroy(bp_net* net) {
   free_ptr(net->seq_in);
   free_ptr(net->W);
   free_ptr(net->V);
-  free_ptr(net->arrivals);
   if (net->host_sse) (void)hipHostFree(net->host_sse);
   if (net->stage) (void)hipHostFree(net->stage);
   for (hipEvent_t e : net->stage_ev)
@@ -1114,9 +1129,6 @@ int bp_set_weights(bp_net* net, const float* w_host, int64_t n) {
   BP_HIP(net, hipStreamSynchronize(net->stream));
   BP_HIP(net, hipMemsetAsync(net->W, 0, sizeof(float) * net->wtotal, net->stream));
   BP_HIP(net, hipMemsetAsync(net->V, 0, sizeof(float) * net->wtotal, net->stream));
-  // the split-K arrival counters are zero between launches; clear them here too,
-  // in case a failed launch left some set
-  BP_HIP(net, hipMemsetAsync(net->arrivals, 0, sizeof(int) * bpk::kMaxArrivals, net->stream));
   return copy_layers(net, net->W, w_host, nullptr);
 }
 
