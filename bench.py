@@ -66,7 +66,7 @@ KERNEL_NAMES = {
     "output_finish": "output_finish_kernel",
     "seq_in": "seq_assemble_kernel",
     "seq_pair": "elman_pair_kernel",
-    "seq_win": "elman_window_kernel",
+    "seq_win": "elman_window_kernel|elman_resident_kernel",
 }
 SMALL_MAX_HIDDEN, SMALL_MAX_OUT, SMALL_MAX_ACTIVE = 256, 64, 32   # the library's fused-path limits
 
@@ -474,7 +474,7 @@ def kind_of_kernel(name):
     if "bias_update_kernel" in name:                           # (likewise)
         return "bias"
     for k, v in KERNEL_NAMES.items():
-        if "<" not in v and v in name:
+        if "<" not in v and any(n in name for n in v.split("|")):
             return k
     return None
 

@@ -50,6 +50,9 @@ int colsum_rows(int M);
 hipError_t forward_layer(hipStream_t s, const float* A, int lda, const float* W, int ldw, int M, int N,
                          int K, const float* bias, float* out, int ldo, const float* tab);
 
+// Estimated microseconds of that launch.
+double forward_us(int M, int N, int K);
+
 // The first layer of an Elman step with its input built in the product
 // (section 10.5): A[m][k] = X[m][k] (X rows n_ext wide) for k < n_ext and
 // cont[m] H[m][k - n_ext] for k in [n_ext, K), H the previous step's first
@@ -224,8 +227,9 @@ hipError_t seq_assemble(hipStream_t s, const float* X, int n_ext, const float* c
 // hidden units, output units and output deltas, with no exchange between
 // blocks.  Step k of the window is rows k * S .. k * S + S - 1 of H, rows, D
 // (and of X, cont, mask, T, each given at the window's first step).  Block b
-// writes the error sum of its rows of step k to sse[k * blocks + b] and the
-// column sums of its deltas over the whole window to colsum row b, blocks =
+// writes error sums of its rows to sse[k * blocks + b], k < steps (they add up
+// to the window's), and the column sums of its deltas over the whole window to
+// colsum row b, blocks =
 // elman_window_blocks(S).  Only for elman_window_fits(...); otherwise, or
 // for a missing pointer, hipErrorInvalidValue.
 struct ElmanWindow {
@@ -255,7 +259,11 @@ struct ElmanWindow {
   double* sse;             // [steps * blocks]
   const float* tab;
   int S, steps;
+  float* out = nullptr;    // forward pass: output units [steps * S][ldo] (T, mask, H, rows, D, colsum, sse unused)
+  int ldo = 0;
 };
+// A forward pass (out set) also needs elman_forward_fits(...).
+bool elman_forward_fits(int S, int n_ext, int n0, int n1, int n2);
 bool elman_window_fits(int S, int n_ext, int n0, int n1, int n2);
 int elman_window_blocks(int S);
 hipError_t elman_window(hipStream_t s, const ElmanWindow& w);

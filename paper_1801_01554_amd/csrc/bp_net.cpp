@@ -949,6 +949,30 @@ int train_sequences(bp_net* net, const float* X, const float* targets, const flo
 int forward_sequences(bp_net* net, const float* X, const float* cont, int64_t T, int S, float* out) {
   if (T == 0) return BP_OK;
   const int L = net->L, n_ext = net->n[0] - net->n_ctx, nL = net->n[L];
+  // one hidden layer: every step in one launch, each block carrying the
+  // recurrence of its own streams
+  if (net->ctx_in_order && L == 2 && bpk::elman_forward_fits(S, n_ext, net->n[0], net->n[1], nL)) {
+    bpk::ElmanWindow ew{};
+    ew.n_ext = n_ext;
+    ew.W0 = wl(net, 0);
+    ew.ldw0 = net->ldw[0];
+    ew.b0 = wbias(net, 0);
+    ew.W1 = wl(net, 1);
+    ew.ldw1 = net->ldw[1];
+    ew.b1 = wbias(net, 1);
+    ew.n0 = net->n[0];
+    ew.n1 = net->n[1];
+    ew.n2 = nL;
+    ew.tab = net->sig_tab;
+    ew.S = S;
+    ew.X = n_ext > 0 ? X : nullptr;
+    ew.cont = cont;
+    ew.steps = (int)T;
+    ew.out = out;
+    ew.ldo = nL;
+    BP_LAUNCH(net, BP_K_SEQ_WIN, bpk::elman_window(net->stream, ew));
+    return BP_OK;
+  }
   int rc = ensure_workspace(net, 2 * (int64_t)S, 0, 0);
   if (rc) return rc;
   rc = ensure_seq_in(net, S);

@@ -82,7 +82,7 @@ __device__ __forceinline__ void load_cols(float* d, const float* p) {
 // multiplied, and the first D - 1 are loaded by prefetch(), which a caller
 // issues ahead of the product.  Rows past K and columns past ldb - C are
 // clamped to valid addresses (their A is zero or their columns unused).
-template <int RG, int C, int D>
+template <int RG, int C, int D, int NW = 4>   // NW waves share K
 struct WinProduct {
   float ring[D][4][C];
   const float* bl;
@@ -91,7 +91,7 @@ struct WinProduct {
   __device__ __forceinline__ void init(const float* __restrict__ B, int ldb_, int K_, int wave, int lane) {
     K = K_;
     ldb = ldb_;
-    const int kc = ((K + 15) >> 4) << 2;
+    const int kc = (K + 4 * NW - 1) / (4 * NW) * 4;
     // the wave's range is uniform across its lanes: row addresses stay scalar
     k0 = __builtin_amdgcn_readfirstlane(wave * kc);
     nit = K > k0 ? (min(kc, K - k0) + 3) >> 2 : 0;
@@ -164,11 +164,11 @@ struct WinProduct {
 
 // The same product with B held in LDS (K x 64 columns, row stride 64, zero
 // rows from K to the end of the last wave's range): one column per lane.
-template <int RG>
+template <int RG, int NW = 4>
 struct WinProductLds {
   int k0, nit;
   __device__ __forceinline__ void init(int K, int wave) {
-    const int kc = ((K + 15) >> 4) << 2;
+    const int kc = (K + 4 * NW - 1) / (4 * NW) * 4;
     k0 = __builtin_amdgcn_readfirstlane(wave * kc);
     nit = K > k0 ? (min(kc, K - k0) + 3) >> 2 : 0;
   }
@@ -448,6 +448,229 @@ __global__ __launch_bounds__(kWinThreads) void elman_window_kernel(ElmanWindow p
   }
 }
 
+// The same window with W0 resident: the register files of a CU hold 512 KB,
+// and 8 waves (two per SIMD, 256 registers each) take the whole of a W0 of up
+// to 320 x 256, KQ k of C1 columns per lane, loaded once per launch instead of
+// streamed from L2 every step, which bounded the kernel above.  What bounds this
+// one is the chain of a step: 2 KQ C1 v_mfma_f32_4x4x1 per SIMD (1.2 us for
+// 320 x 256), LDS round trips and three barriers.  (With 4 waves of 512
+// registers the compiler moves the upper half of W0 through one register: 10.0
+// us a step.)  There is no wave to spare for memory traffic, and none is
+// needed: the inputs, flags and targets of the next step are loaded a step
+// ahead into registers, and stores have most of a step before a later load
+// waits behind them.  Elementwise work maps thread t to column t % 256 of rows
+// 2 (t / 256) and the next.
+//
+// Per step k, between barriers:
+//   1. output units, deltas of step k - 1; loads for steps k, k + 1; hidden product
+//   2. hidden units
+//   3. output product; input rows k + 1 (X, flag x hidden k)
+// With p.out set it is a forward pass: the output units go there, and targets,
+// deltas and the rows of the change products are left out.
+// 320-256-64, 1024 streams: a training step 7.5 -> 6.0 us (windows of 8, the
+// load of W0 included), a forward step 3.5 (streaming: 6.4; a launch per layer: 13.8).
+constexpr int kResWaves = 8, kResThreads = 64 * kResWaves;
+template <int C1, int C2, int KQ>
+__global__ __launch_bounds__(kResThreads) void elman_resident_kernel(ElmanWindow p) {
+  constexpr int R = 4, RT = 2;                                          // rows; rows per thread
+  constexpr int NW = kResWaves;
+  constexpr int AS = kWinMaxIn + 4, HS = kWinMaxUnits + 4;
+  static_assert(KQ % 4 == 0 && NW * KQ <= kWinMaxIn && R * kWinMaxUnits == RT * kResThreads, "shape");
+  __shared__ __attribute__((aligned(16))) float Arow[R * AS];           // input rows of the step
+  __shared__ __attribute__((aligned(16))) float Hrow[R * HS];           // hidden units of the step
+  __shared__ __attribute__((aligned(16))) float P1[NW * R * 64 * C1];   // per-wave partial products
+  __shared__ __attribute__((aligned(16))) float P2[NW * R * 64 * C2];
+  __shared__ double red[NW];
+  __shared__ float csl[kWinMaxUnits];
+  __shared__ __attribute__((aligned(16))) float W1s[C2 == 1 ? (kWinMaxUnits + 4) * 64 : 4];
+  const int tid = threadIdx.x, lane = tid & 63, col = tid & 255, i0 = (tid >> 8) * RT;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int S = p.S, n_ext = p.n_ext, n0 = p.n0, n1 = p.n1, n2 = p.n2, n_ctx = n0 - n_ext;
+  const int m0 = blockIdx.x * R, rows_in = min(R, S - m0), steps = p.steps;
+  const bool train = p.out == nullptr;
+
+  // W0: rows k0 .. k0 + KQ - 1 of this lane's C1 columns (zero past n0, where Arow is zero too)
+  const int k0 = wave * KQ;
+  float w0[KQ][C1];
+  {
+    const float* b = p.W0 + min(C1 * lane, p.ldw0 - C1);
+#pragma unroll
+    for (int k = 0; k < KQ; ++k) load_cols<C1>(w0[k], b + (size_t)min(k0 + k, n0 - 1) * p.ldw0);
+#pragma unroll
+    for (int k = 0; k < KQ; ++k)
+#pragma unroll
+      for (int c = 0; c < C1; ++c) w0[k][c] = k0 + k < n0 ? w0[k][c] : 0.f;
+  }
+  for (int e = tid; e < R * AS; e += kResThreads) Arow[e] = 0.f;
+  for (int e = tid; e < R * HS; e += kResThreads) {
+    const int i = e / HS, c = e - i * HS;
+    Hrow[e] = p.Hprev && c < n_ctx && i < rows_in ? p.Hprev[(size_t)(m0 + i) * p.ldhp + c] : 0.f;
+  }
+  if constexpr (C2 == 1)
+    for (int e = tid; e < (n1 + 4) * 64; e += kResThreads) {
+      const int kk = e >> 6, c = e & 63;
+      W1s[e] = kk < n1 && c < n2 ? p.W1[(size_t)kk * p.ldw1 + c] : 0.f;
+    }
+  WinProduct<1, C2, 2, NW> po;
+  WinProductLds<1, NW> pol;
+  if constexpr (C2 == 1) pol.init(n1, wave);
+  else po.init(p.W1, p.ldw1, n1, wave, lane);
+  const float bh = col < n1 ? p.b0[col] : 0.f, bo = col < n2 ? p.b1[col] : 0.f;
+
+  // rows past the streams read the last stream's (their results go nowhere)
+  float xr[RT], cr[RT], tr[RT], mr[RT];
+  const int xc = min(col, max(n_ext - 1, 0)), tc = min(col, n2 - 1);
+  auto row_of = [&](int k, int i) { return (size_t)k * S + m0 + min(i0 + i, rows_in - 1); };
+  auto load_x = [&](int k) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      xr[i] = n_ext > 0 ? p.X[row_of(k, i) * n_ext + xc] : 0.f;
+      cr[i] = p.cont[row_of(k, i)];
+    }
+  };
+  auto load_t = [&](int k) {
+#pragma unroll
+    for (int i = 0; i < RT; ++i) {
+      tr[i] = p.T[row_of(k, i) * p.ldt + tc];
+      mr[i] = p.mask ? p.mask[row_of(k, i)] : 1.f;
+    }
+  };
+  // input rows of step k: external inputs, then flag x context (zero past the streams)
+  auto build_rows = [&](int k) {
+    if (col < n_ext) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        Arow[(i0 + i) * AS + col] = xr[i];
+        if (train && i0 + i < rows_in) p.rows[row_of(k, i) * p.ldr + col] = xr[i];
+      }
+    }
+    if (col < n_ctx) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        const float v = i0 + i < rows_in ? cr[i] * Hrow[(i0 + i) * HS + col] : 0.f;
+        Arow[(i0 + i) * AS + n_ext + col] = v;
+        if (train && i0 + i < rows_in) p.rows[row_of(k, i) * p.ldr + n_ext + col] = v;
+      }
+    }
+  };
+  double sse = 0.0;     // this thread's error, and sum of deltas, over the window
+  float csum = 0.f;
+  auto outputs = [&](int k) {
+    if (col < n2) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        float z = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) z += P2[(w * R + i0 + i) * (64 * C2) + col];
+        const float y = unit_sigma(z + bo, p.tab);
+        if (i0 + i < rows_in) {
+          if (train) {
+            const float err = (tr[i] - y) * mr[i], d = err * y * (1.0f - y);
+            sse += (double)(err * err);
+            p.D[row_of(k, i) * p.ldd + col] = d;
+            csum += d;
+          } else {
+            p.out[row_of(k, i) * p.ldo + col] = y;
+          }
+        }
+      }
+    }
+  };
+
+  load_x(0);
+  __syncthreads();
+  build_rows(0);
+  __syncthreads();
+  for (int k = 0; k < steps; ++k) {
+    if (k > 0) outputs(k - 1);
+    if (train) load_t(k);
+    load_x(min(k + 1, steps - 1));
+    if constexpr (C2 != 1) po.prefetch();
+    {
+      constexpr int NA = 4 / C1;
+      f32x4 acc[NA][C1];
+#pragma unroll
+      for (int h = 0; h < NA; ++h)
+#pragma unroll
+        for (int c = 0; c < C1; ++c) acc[h][c] = f32x4{0.f, 0.f, 0.f, 0.f};
+      const float* ar = Arow + (lane & 3) * AS + k0;
+#pragma unroll
+      for (int g = 0; g < KQ / 4; ++g) {
+        const f32x4 av = *reinterpret_cast<const f32x4*>(ar + 4 * g);
+#pragma unroll
+        for (int j = 0; j < 4; ++j)
+#pragma unroll
+          for (int c = 0; c < C1; ++c)
+            acc[j % NA][c] = __builtin_amdgcn_mfma_f32_4x4x1f32(av[j], w0[4 * g + j][c], acc[j % NA][c], 0, 0, 0);
+      }
+#pragma unroll
+      for (int r = 0; r < R; ++r)
+#pragma unroll
+        for (int c = 0; c < C1; ++c) {
+          float v = acc[0][c][r];
+#pragma unroll
+          for (int h = 1; h < NA; ++h) v += acc[h][c][r];
+          P1[(wave * R + r) * (64 * C1) + C1 * lane + c] = v;
+        }
+    }
+    __syncthreads();
+    if (col < n1) {
+#pragma unroll
+      for (int i = 0; i < RT; ++i) {
+        float z = 0.f;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) z += P1[(w * R + i0 + i) * (64 * C1) + col];
+        const float hv = unit_sigma(z + bh, p.tab);
+        Hrow[(i0 + i) * HS + col] = hv;
+        if (train && i0 + i < rows_in) p.H[row_of(k, i) * p.ldh + col] = hv;
+      }
+    }
+    __syncthreads();
+    if constexpr (C2 == 1) pol.run(Hrow, HS, W1s, P2, wave, lane);
+    else po.run(Hrow, HS, P2, wave, lane);
+    if (k + 1 < steps) build_rows(k + 1);
+    __syncthreads();
+  }
+  outputs(steps - 1);
+  if (train) {
+    // column sums: rows 0, 1, then rows 2, 3; the window's error in the first
+    // step's partial, zero in the others'
+    if (i0 > 0) csl[col] = csum;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sse += __shfl_down(sse, o);
+    if (lane == 0) red[wave] = sse;
+    __syncthreads();
+    if (i0 == 0 && col < n2) p.colsum[(size_t)blockIdx.x * p.ldcs + col] = csum + csl[col];
+    if (tid == 0) {
+      double t = 0.0;
+      for (int w = 0; w < NW; ++w) t += red[w];
+      p.sse[blockIdx.x] = t;
+    }
+    for (int k = 1 + tid; k < steps; k += kResThreads) p.sse[(size_t)k * gridDim.x + blockIdx.x] = 0.0;
+  }
+}
+
+// k per wave of the resident kernel for n0 inputs and C1 columns per lane: the
+// smallest built size that covers n0; 0 when W0 does not fit.
+int win_resident_kq(int n0, int C1) {
+  const int small = C1 == 4 ? 20 : 32, large = C1 == 4 ? 40 : 64;
+  return n0 <= kResWaves * small ? small : n0 <= kResWaves * large ? large : 0;
+}
+
+template <int C1, int KQ>
+hipError_t launch_resident_c2(hipStream_t s, const ElmanWindow& w, int C2) {
+  const unsigned blocks = (unsigned)elman_window_blocks(w.S);
+  if (C2 == 1) return launch_kernel(elman_resident_kernel<C1, 1, KQ>, blocks, kResThreads, 0, s, w);
+  if (C2 == 2) return launch_kernel(elman_resident_kernel<C1, 2, KQ>, blocks, kResThreads, 0, s, w);
+  return launch_kernel(elman_resident_kernel<C1, 4, KQ>, blocks, kResThreads, 0, s, w);
+}
+
+hipError_t launch_resident(hipStream_t s, const ElmanWindow& w, int C1, int C2, int kq) {
+  if (C1 == 4) return kq == 20 ? launch_resident_c2<4, 20>(s, w, C2) : launch_resident_c2<4, 40>(s, w, C2);
+  if (C1 == 2) return kq == 32 ? launch_resident_c2<2, 32>(s, w, C2) : launch_resident_c2<2, 64>(s, w, C2);
+  return kq == 32 ? launch_resident_c2<1, 32>(s, w, C2) : launch_resident_c2<1, 64>(s, w, C2);
+}
+
 template <int RG, int C1>
 hipError_t launch_window_c2(hipStream_t s, const ElmanWindow& w, int C2) {
   const unsigned blocks = (unsigned)elman_window_blocks(w.S);
@@ -460,6 +683,19 @@ int cols_per_lane(int n) { return n <= 64 ? 1 : (n <= 128 ? 2 : 4); }
 
 }  // namespace
 
+// A forward pass takes the resident kernel where its estimate per step (one
+// round of blocks per 256; measured 3.5 us for 320-256-64, 1.7 for 68-48-12,
+// 6.0 for 316-256-200, whose W1 streams from L2) is below that of a launch per
+// layer (6 us each while the streams are few: 13.8 us a step for 320-256-64 at
+// 1024 streams).
+bool elman_forward_fits(int S, int n_ext, int n0, int n1, int n2) {
+  if (!elman_window_fits(S, n_ext, n0, n1, n2)) return false;
+  const int C1 = cols_per_lane(n1), kq = win_resident_kq(n0, C1);
+  const double step_us = 1.6 + 0.012 * kq * C1 + (n2 > 64 ? n1 * n2 * 4e-5 : 0.0);
+  const int rounds = (elman_window_blocks(S) + 255) / 256;
+  return kq > 0 && rounds * step_us < forward_us(S, n1, n0) + forward_us(S, n2, n1);
+}
+
 bool elman_window_fits(int S, int n_ext, int n0, int n1, int n2) {
   return S > 0 && n_ext >= 0 && n_ext <= 256 && n_ext <= n0 && n0 - n_ext <= n1 && n0 >= 1 &&
          n0 <= kWinMaxIn && n1 >= 1 && n1 <= kWinMaxUnits && n2 >= 1 && n2 <= kWinMaxUnits;
@@ -468,19 +704,26 @@ bool elman_window_fits(int S, int n_ext, int n0, int n1, int n2) {
 int elman_window_blocks(int S) { return (S + 4 * kWinRG - 1) / (4 * kWinRG); }
 
 hipError_t elman_window(hipStream_t s, const ElmanWindow& w) {
+  const int C1 = cols_per_lane(w.n1), C2 = cols_per_lane(w.n2), kq = win_resident_kq(w.n0, C1);
+  const bool train = !w.out;
   if (!elman_window_fits(w.S, w.n_ext, w.n0, w.n1, w.n2) || w.steps < 1 || (w.n_ext > 0 && !w.X) || !w.cont ||
-      !w.T || !w.W0 || !w.b0 || !w.W1 || !w.b1 || !w.H || !w.rows || !w.D || !w.colsum || !w.sse)
+      !w.W0 || !w.b0 || !w.W1 || !w.b1 || (!train && (kq == 0 || w.ldo < w.n2)) ||
+      (train && (!w.T || !w.H || !w.rows || !w.D || !w.colsum || !w.sse)))
     return hipErrorInvalidValue;
-  const int C1 = cols_per_lane(w.n1), C2 = cols_per_lane(w.n2);
   // 16-byte aligned rows: weights wide enough for the column loads, outputs
   // for 16-byte stores up to the next multiple of 4 columns
   auto rows16 = [](const void* q, int ld, int n) {
     return (reinterpret_cast<uintptr_t>(q) & 15) == 0 && (ld & 3) == 0 && ld >= ((n + 3) & ~3);
   };
-  if (!rows16(w.W0, w.ldw0, w.n1) || !rows16(w.W1, w.ldw1, w.n2) || !rows16(w.rows, w.ldr, w.n0) ||
-      !rows16(w.H, w.ldh, w.n1) || !rows16(w.D, w.ldd, w.n2) || w.ldt < w.n2 || w.ldcs < w.n2 ||
-      (w.Hprev && w.ldhp < w.n0 - w.n_ext))
+  if (!rows16(w.W0, w.ldw0, w.n1) || !rows16(w.W1, w.ldw1, w.n2) || (w.Hprev && w.ldhp < w.n0 - w.n_ext) ||
+      (train && (!rows16(w.rows, w.ldr, w.n0) || !rows16(w.H, w.ldh, w.n1) || !rows16(w.D, w.ldd, w.n2) ||
+                 w.ldt < w.n2 || w.ldcs < w.n2)))
     return hipErrorInvalidValue;
+  // W0 too large for the registers, or too large beside a ring of streamed
+  // output weights four columns wide (training 316-256-200 in windows of 4: no
+  // faster, 11.2 us a step; 300-200-100 in windows of 8: 6.7 against 8.1):
+  // streamed from L2 every step
+  if (kq > 0 && !(train && C1 == 4 && kq == 40 && C2 == 4)) return launch_resident(s, w, C1, C2, kq);
   if (C1 == 1) return launch_window_c2<kWinRG, 1>(s, w, C2);
   if (C1 == 2) return launch_window_c2<kWinRG, 2>(s, w, C2);
   return launch_window_c2<kWinRG, 4>(s, w, C2);

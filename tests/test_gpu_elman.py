@@ -240,3 +240,72 @@ def test_elman_runs_are_identical(dev):
         out.append((sse, net.get_weights()))
     assert out[0][0] == out[1][0]
     np.testing.assert_array_equal(out[0][1], out[1][1])
+
+
+# external inputs, hidden units, outputs, context units, streams, steps, window:
+# W0 resident in registers at the ends of each built size (160 and 320 inputs
+# for 129-256 hidden units, 256 and 512 for fewer), one past them (streamed), a
+# context smaller than the hidden layer, no external inputs, output widths on
+# both sides of 64 and 128, streams that leave a block 1-3 of its 4 rows, one
+# step, and so many streams that a forward pass goes layer by layer
+WINDOW_SHAPES = [
+    (64, 256, 64, 256, 37, 5, 2), (65, 256, 65, 256, 6, 3, 2), (32, 129, 3, 128, 9, 4, 4), (33, 130, 129, 128, 5, 3, 1),
+    (256, 256, 64, 255, 7, 3, 3), (128, 128, 128, 128, 4, 4, 3), (129, 128, 200, 128, 3, 2, 2), (0, 64, 7, 64, 11, 6, 4),
+    (200, 64, 64, 56, 1, 5, 2), (10, 20, 4, 9, 2, 1, 1), (30, 200, 20, 200, 30000, 2, 2),
+]
+
+
+@pytest.mark.parametrize("n_ext,n1,n2,n_ctx,S,T,window", WINDOW_SHAPES)
+@pytest.mark.parametrize("table", [False, True])
+def test_one_launch_windows(dev, n_ext, n1, n2, n_ctx, S, T, window, table):
+    print(f"one-launch windows: {n_ext}+{n_ctx}-{n1}-{n2} streams={S} steps={T} window={window} table={table}", flush=True)
+    g = torch.Generator(device=dev)
+    g.manual_seed(n_ext + n1 + n2 + S)
+    sizes = (n_ext + n_ctx, n1, n2)
+    X = torch.randn((T, S, n_ext), generator=g, device=dev)
+    cont = (torch.rand((T, S), generator=g, device=dev) < 0.8).float()
+    mask = (torch.rand((T, S), generator=g, device=dev) < 0.8).float()
+    t = torch.rand((T, S, n2), generator=g, device=dev)
+    w = wl.draw_weights(3, sizes, "fanin")
+    W0 = torch.from_numpy(w[:(sizes[0] + 1) * n1].astype(np.float64)).view(-1, n1).to(dev)
+    W1 = torch.from_numpy(w[(sizes[0] + 1) * n1:].astype(np.float64)).view(-1, n2).to(dev)
+
+    def sigma(z):
+        if not table:
+            return torch.sigmoid(z)
+        entry = torch.sigmoid(-15.0 + 30.0 * torch.arange(256, dtype=torch.float64, device=dev) / 255.0)
+        x1 = (z.clamp(-15.0, 15.0) + 15.0) * 8.5
+        i = x1.floor().clamp(max=254).long()
+        return entry[i] + (x1 - i) * (entry[i + 1] - entry[i])
+
+    net = bp.Net(sizes)
+    try:
+        net.set_weights(w)
+        net.set_context([1] * n_ctx, list(range(n_ctx)))
+        if table:
+            net.set_sigmoid(bp.BP_SIGMOID_TABLE)
+        y = net.forward_sequences(X, cont).double()
+        sse = net.train_sequences(X[:window].contiguous(), t[:window].contiguous(), cont[:window].contiguous(),
+                                  mask[:window].contiguous(), window, 1.0, 0.0)
+        V = torch.from_numpy(net.get_momentum().astype(np.float64)).to(dev)
+    finally:
+        net.close()
+    h = torch.zeros((S, n1), dtype=torch.float64, device=dev)
+    G0, G1, err = torch.zeros_like(W0), torch.zeros_like(W1), 0.0
+    one = torch.ones((S, 1), dtype=torch.float64, device=dev)
+    for k in range(T):
+        x = torch.cat([X[k].double(), cont[k].double()[:, None] * h[:, :n_ctx]], 1)
+        h = sigma(x @ W0[:-1] + W0[-1])
+        o = sigma(h @ W1[:-1] + W1[-1])
+        # fp32 sums of at most 512 and 256 terms, twice; the recurrence damps earlier errors
+        assert float((y[k] - o).abs().max()) < 2e-6, k
+        if k < window:
+            e = (t[k].double() - o) * mask[k].double()[:, None]
+            err += float((e * e).sum())
+            d = e * o * (1 - o)
+            G1 += torch.cat([h, one], 1).T @ d
+            G0 += torch.cat([x, one], 1).T @ ((d @ W1[:-1].T) * h * (1 - h))
+    assert abs(sse - err) <= 1e-5 * max(err, 1e-6)
+    got0, got1 = V[:G0.numel()].view_as(G0), V[G0.numel():].view_as(G1)
+    for got, ref in ((got0, G0), (got1, G1)):
+        assert float((got - ref).abs().max()) <= 1e-5 * float(ref.abs().max())   # (0 where every pattern is masked)
