@@ -58,7 +58,7 @@ KERNEL_NAMES = {
     "change": "gemm_kernel<..., EpiUpdate>",
     "splitk": "gemm_kernel|skinny_kernel<..., EpiChangePartial>",
     "bias": "update_finish_kernel",
-    "gather": "onehot_forward_kernel",
+    "gather": "onehot_forward_kernel|onehot_net_kernel",
     "scatter": "onehot_update_kernel",
     "reduce": "sse_reduce_kernel",
     "fused_fb": "small_fwdbwd_kernel",

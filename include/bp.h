@@ -259,7 +259,8 @@ enum {
                       /* (partial sums, added and applied by BP_K_BIAS)    */
   BP_K_BIAS = 5,      /* end of an update: bias rows' column sums and split */
                       /* changes' partials in split order + momentum update */
-  BP_K_GATHER = 6,    /* one-hot first-layer forward                        */
+  BP_K_GATHER = 6,    /* one-hot first-layer forward (or a whole two-layer  */
+                      /* forward pass)                                      */
   BP_K_SCATTER = 7,   /* one-hot first-layer change + momentum update       */
   BP_K_REDUCE = 8,    /* epoch error reduction                              */
   BP_K_FUSED_FB = 9,  /* small one-hot nets: whole forward + backward pass  */

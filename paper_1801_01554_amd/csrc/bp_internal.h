@@ -163,6 +163,14 @@ hipError_t onehot_forward(hipStream_t s, const int32_t* act, int n_active, int r
                           int n0, int H, int mode, float* out, int ldo, const float* T, int ldt,
                           double* sse_part, const float* tab);
 
+// Forward pass of a one-hot net with one hidden layer, both layers in one
+// launch: out[p][j] = sigma(W1[H][j] + sum_i sigma(net[p][i]) W1[i][j]), net as
+// above, rows of W0 padded to a multiple of 4 floats.  Taken where
+// onehot_net_fits(...): where it is faster than a launch per layer.
+bool onehot_net_fits(int64_t rows, int n_active, int H, int O);
+hipError_t onehot_net(hipStream_t s, const int32_t* act, int n_active, int rows, const float* W0, int ldw0, int n0,
+                      int H, const float* W1, int ldw1, int O, float* out, int ldo, const float* tab);
+
 // One-hot first-layer change and update of the n0 weight rows and, with
 // `bias_row`, the bias row (D rows 16-byte aligned, ldd a multiple of 4):
 //   G[r][j] = sum over patterns p containing index r of D[p][j]  (r < n0),

@@ -1212,6 +1212,111 @@ __global__ __launch_bounds__(kThreads) void onehot_forward_kernel(const int32_t*
   }
 }
 
+// Forward pass of a one-hot net with one hidden layer in one launch.  A block
+// takes 32 patterns and walks the hidden units in chunks of CW = 64 KG: each
+// pass of its 512 threads gathers 32 / KG patterns (four adjacent units per
+// thread, as onehot_forward_kernel), the units' activations go to LDS, and the
+// chunk is multiplied with its rows of W1, loaded before the gather, by
+// v_mfma_f32_32x32x2_f32: wave w owns outputs 32 (w % NS) .. + 31 and one of 8 /
+// NS ranges of the chunk's units (lane (h, r) holds unit 8 g + 4 h + t of MFMA t
+// of group g).  The ranges' sums are added in order.  What bounds it: the rows
+// gathered from L2 (203-120-26 at 100000 patterns: 35 us, 384 MB of rows, 11
+// TB/s), and for short calls the chain index, row, product.  Against a launch
+// per layer and per 8192 patterns, with the table: 203-120-26 at 20000 patterns
+// 50.6 -> 11.8 us, at 8 patterns 9.6 -> 6.3.  (Chunks of 256 and every wave on
+// all strips: registers spill, 203-512-64 at 20000 patterns 102 us against 49.)
+constexpr int kNetRows = 32, kNetThreads = 512, kNetMaxOut = 128;
+template <int KG, int NS>
+__global__ __launch_bounds__(kNetThreads, 4) void onehot_net_kernel(const int32_t* __restrict__ act, int n_active,
+                                                                    int rows, const float* __restrict__ W0, int ldw0,
+                                                                    int n0, int H, const float* __restrict__ W1,
+                                                                    int ldw1, int O, float* __restrict__ out, int ldo,
+                                                                    const float* __restrict__ tab) {
+  constexpr int NW = kNetThreads / 64, NR = NW / NS, CW = 64 * KG, RS = CW + 4;   // waves; ranges; chunk; LDS row
+  constexpr int NG = CW / NR / 8;                                         // 8-unit groups of a range
+  constexpr int LP = CW / 4, PP = kNetThreads / LP, NP = kNetRows / PP;   // lanes per pattern, patterns per pass, passes
+  constexpr int kIn = NS == 4 ? 5 : 8;                                    // rows in flight per pass (128 registers)
+  static_assert(NR * NG * 8 == CW && PP * NP == kNetRows, "shape");
+  constexpr int kHid = kNetRows * RS, kPart = NW * 1024;
+  __shared__ __attribute__((aligned(16))) float lds[kHid > kPart ? kHid : kPart];
+  const int tid = threadIdx.x, lane = tid & 63, r = lane & 31, h = lane >> 5;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), n1 = 32 * (wave % NS) + r, u0 = wave / NS * NG * 8;
+  const int64_t p0 = (int64_t)blockIdx.x * kNetRows;
+  const int n_rows = (int)min((int64_t)kNetRows, rows - p0);
+  f32x16 acc;
+#pragma unroll
+  for (int e = 0; e < 16; ++e) acc[e] = 0.f;
+  for (int c0 = 0; c0 < H; c0 += CW) {
+    float b[NG][4];
+#pragma unroll
+    for (int g = 0; g < NG; ++g)
+#pragma unroll
+      for (int t = 0; t < 4; ++t)
+        b[g][t] = W1[(size_t)min(c0 + u0 + 8 * g + 4 * h + t, H - 1) * ldw1 + min(n1, O - 1)];
+    const int cl = 4 * (tid % LP), col = c0 + cl, colc = min(col, ldw0 - 4);
+    {
+      const int32_t* a[NP];
+      f32x4 net[NP];
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        // rows past the patterns repeat the last one (their outputs go nowhere)
+        a[i] = act + (p0 + min(tid / LP + PP * i, n_rows - 1)) * n_active;
+        net[i] = *reinterpret_cast<const f32x4*>(W0 + (size_t)n0 * ldw0 + colc);
+      }
+      for (int k0 = 0; k0 < n_active; k0 += kIn) {
+        int ix[NP][kIn];
+        f32x4 v[NP][kIn];
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+#pragma unroll
+          for (int k = 0; k < kIn; ++k) ix[i][k] = k0 + k < n_active ? a[i][min(k0 + k, n_active - 1)] : -1;
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+#pragma unroll
+          for (int k = 0; k < kIn; ++k) v[i][k] = row_at(W0, ldw0, n0, ix[i][k], colc);
+#pragma unroll
+        for (int i = 0; i < NP; ++i)
+#pragma unroll
+          for (int k = 0; k < kIn; ++k)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) net[i][q] = (unsigned)ix[i][k] < (unsigned)n0 ? net[i][q] + v[i][k][q] : net[i][q];
+      }
+#pragma unroll
+      for (int i = 0; i < NP; ++i) {
+        f32x4 y;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) y[q] = col + q < H ? unit_sigma(net[i][q], tab) : 0.f;
+        *reinterpret_cast<f32x4*>(lds + (tid / LP + PP * i) * RS + cl) = y;
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      const f32x4 av = *reinterpret_cast<const f32x4*>(lds + r * RS + u0 + 8 * g + 4 * h);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const float bv = c0 + u0 + 8 * g + 4 * h + t < H ? b[g][t] : 0.f;
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(av[t], bv, acc, 0, 0, 0);
+      }
+    }
+    __syncthreads();                                   // the chunk is read
+  }
+#pragma unroll
+  for (int e = 0; e < 16; ++e) lds[wave * 1024 + e * 64 + lane] = acc[e];
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < NS * 1024 / kNetThreads; ++j) {
+    const int f = tid + j * kNetThreads, strip = f >> 10, q = f & 1023, e = q >> 6;
+    const int m = 8 * (e >> 2) + 4 * h + (e & 3), n = 32 * strip + r;
+    if (m < n_rows && n < O) {
+      float z = 0.f;
+#pragma unroll
+      for (int w = 0; w < NR; ++w) z += lds[(w * NS + strip) * 1024 + q];
+      out[(p0 + m) * ldo + n] = unit_sigma(z + W1[(size_t)H * ldw1 + n], tab);
+    }
+  }
+}
+
 // One-hot first-layer change + update.  Block (r, c): weight row r (r == n0 is
 // the bias row) and columns [1024 c, 1024 c + 1024).  Every block searches the
 // batch's indices, 16384 at a time (16 per thread, read 16 bytes at a time in
@@ -1683,6 +1788,43 @@ hipError_t onehot_forward(hipStream_t s, const int32_t* act, int n_active, int r
   const int lp = column_lanes(H, 64), strips = (H + 4 * lp - 1) / (4 * lp);
   return launch_kernel(onehot_forward_kernel, onehot_forward_blocks(rows, H), kThreads, 0, s, act, n_active, rows, W0,
                        ldw, n0, H, lp, strips, mode, out, ldo, T, ldt, sse_part, tab);
+}
+
+// One block's chain decides while all blocks run at once (up to 16384
+// patterns): 2.5 us and, per chunk, the gather's rounds and the product.  The
+// launches per layer take about 10 us for short calls (203-120-26 at 1000
+// patterns: 10.2 us against 6.8), and from 4096 patterns on more (203-250-61 at
+// 5000: 16.3 us against 13.1); from 8192 patterns on, which they
+// split into pieces, they take longer at every width measured (203-1024-26 at
+// 8192: 81 against 27.5; 203-4096-128 at 30000: 1022 against 586).  Below that
+// many chunks lose: 203-1024-26 at 1000 patterns 25 us against 19, 1740-120-61
+// at 4096 17.5 against 13.7.
+bool onehot_net_fits(int64_t rows, int n_active, int H, int O) {
+  if (rows <= 0 || O > kNetMaxOut) return false;
+  if (rows >= 8192) return true;
+  const double gather = O <= 64 ? 1.3 * ((n_active + 7) / 8) : 0.85 * ((n_active + 4) / 5);
+  const double chunk = gather + (O <= 32 ? 1.4 : O <= 64 ? 2.65 : 3.4);
+  return 2.5 + (H + 127) / 128 * chunk <= (rows >= 4096 ? 12.0 : 8.0);
+}
+
+template <int KG>
+static hipError_t launch_onehot_net(hipStream_t s, const int32_t* act, int n_active, int rows, const float* W0,
+                                    int ldw0, int n0, int H, const float* W1, int ldw1, int O, float* out, int ldo,
+                                    const float* tab) {
+  const unsigned blocks = (unsigned)(((int64_t)rows + kNetRows - 1) / kNetRows);
+  auto kernel = O <= 32 ? onehot_net_kernel<KG, 1> : O <= 64 ? onehot_net_kernel<KG, 2> : onehot_net_kernel<KG, 4>;
+  return launch_kernel(kernel, blocks, kNetThreads, 0, s, act, n_active, rows, W0, ldw0, n0, H, W1, ldw1, O, out, ldo,
+                       tab);
+}
+
+hipError_t onehot_net(hipStream_t s, const int32_t* act, int n_active, int rows, const float* W0, int ldw0, int n0,
+                      int H, const float* W1, int ldw1, int O, float* out, int ldo, const float* tab) {
+  if (rows <= 0) return hipSuccess;
+  if (n_active < 1 || n0 < 1 || H < 1 || O < 1 || O > kNetMaxOut || ldw0 < ((H + 3) & ~3) || (ldw0 & 3) || !aligned16(W0) ||
+      ldw1 < O || ldo < O)
+    return hipErrorInvalidValue;
+  auto launch = H <= 64 ? launch_onehot_net<1> : launch_onehot_net<2>;
+  return launch(s, act, n_active, rows, W0, ldw0, n0, H, W1, ldw1, O, out, ldo, tab);
 }
 
 hipError_t onehot_update(hipStream_t s, const int32_t* act, int n_active, int rows, const float* D, int ldd, int n0,

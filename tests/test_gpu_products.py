@@ -182,3 +182,58 @@ def test_onehot_rows(sizes, rows, n_active, checked):
         assert float((got - G).abs().max() / G.abs().max()) < 5e-6, l     # fp32 sums of at most `rows` terms
         assert bool((got[:-1][(acts[l] != 0).sum(0) == 0] == 0).all())    # rows no pattern has stay put
         d = (d @ W[l][:-1].T) * acts[l] * (1 - acts[l])
+
+
+# Forward pass of one-hot nets with one hidden layer: hidden units around the
+# chunks of 64 and 128 and their 8-unit groups, outputs around the strips of 32
+# and past the last (129: a launch per layer), patterns around a block's 32 and
+# the dispatch's 4096 and 8192, active inputs around the 5 and 8 rows in flight.  A
+# hidden unit is off by dh: its sum of n_active + 1 rounded terms through the
+# logistic's slope (or the table's steepest segment), and 4 ulp of its own; an
+# output by the product's bound (one rounding per unit) plus sum |w| dh.  The
+# table adds the rounding of its argument, 256 units of the table at most.
+@pytest.mark.parametrize("hidden,n_out,rows,n_active", [
+    (1, 1, 1, 1), (7, 33, 31, 5), (63, 32, 32, 6), (64, 31, 33, 8), (65, 65, 4095, 9), (127, 64, 4096, 1),
+    (128, 127, 100, 5), (129, 128, 4097, 17), (250, 26, 4500, 16), (301, 60, 8193, 7), (1030, 100, 8192, 33),
+    (1030, 20, 40, 2), (129, 128, 8195, 17), (90, 129, 5000, 4),
+])
+@pytest.mark.parametrize("table", [False, True])
+def test_onehot_two_layer_forward(hidden, n_out, rows, n_active, table):
+    print(f"one-hot forward: hidden={hidden} outputs={n_out} rows={rows} active={n_active} table={table}", flush=True)
+    sizes = (40, hidden, n_out)
+    g = np.random.default_rng(hidden + rows)
+    act = g.integers(0, 40, (rows, n_active)).astype(np.int32)      # a pattern may name a row twice: it counts twice
+    act[rows // 2, 0] = -1                                          # selects no row
+    act[rows - 1, n_active - 1] = 40                                # neither does this
+    w = wl.draw_weights(5, sizes, "uniform0.3")
+    flat = torch.from_numpy(w.astype(np.float64)).cuda()
+    W0, W1 = flat[:41 * hidden].view(41, hidden), flat[41 * hidden:].view(hidden + 1, n_out)
+    a64 = torch.from_numpy(act).cuda().long()
+    x = torch.zeros((rows, 42), dtype=torch.float64, device="cuda")
+    x.scatter_add_(1, torch.where(a64 < 0, 41, a64), torch.ones_like(a64, dtype=torch.float64))
+    x = x[:, :40]
+    entry = torch.sigmoid(-15.0 + 30.0 * torch.arange(256, dtype=torch.float64, device="cuda") / 255.0)
+
+    def sigma(z):
+        if not table:
+            return torch.sigmoid(z)
+        x1 = (z.clamp(-15.0, 15.0) + 15.0) * 8.5
+        i = x1.floor().clamp(max=254).long()
+        return entry[i] + (x1 - i) * (entry[i + 1] - entry[i])
+
+    own = 4 * U + (256 * U * 0.03 if table else 0.0)                # 0.03: the largest step between entries
+    h = sigma(x @ W0[:-1] + W0[-1])
+    dh = 0.25 * (n_active + 1) * U * (x @ W0[:-1].abs() + W0[-1].abs()) + own
+    y = sigma(h @ W1[:-1] + W1[-1])
+    S = h @ W1[:-1].abs() + W1[-1].abs()
+    dy = 0.25 * ((hidden + 9) * U * S + dh @ W1[:-1].abs()) + own
+    net = bp.Net(sizes)
+    try:
+        net.set_weights(w)
+        if table:
+            net.set_sigmoid(bp.BP_SIGMOID_TABLE)
+        got = net.forward(active=torch.from_numpy(act).cuda()).double()
+    finally:
+        net.close()
+    assert got.shape == y.shape
+    assert bool(((got - y).abs() <= dy).all()), float(((got - y).abs() - dy).max())
