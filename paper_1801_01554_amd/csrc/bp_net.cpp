@@ -13,9 +13,9 @@
 #include <cmath>
 #include <cstdio>
 #include <cstring>
+#include <exception>
 #include <mutex>
 #include <string>
-#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -327,8 +327,8 @@ void copy_host(float* dst, const float* src, int64_t n) {
   };
   try {
     for (; started < parts - 1; ++started) helper[started] = std::thread(part, started);
-  } catch (const std::system_error&) {
-    // no more threads: the rest is copied here
+  } catch (const std::exception&) {
+    // no more threads, or no memory for one: the rest is copied here
   }
   for (int i = started; i < parts; ++i) part(i);
   for (int i = 0; i < started; ++i) helper[i].join();
