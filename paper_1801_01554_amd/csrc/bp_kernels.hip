@@ -1,9 +1,10 @@
 // bp_kernels.hip -- gfx950 (CDNA4) kernels of pooled back-propagation, fp32.
 //
 // The three weight contractions of one pooled update (forward, hidden deltas,
-// summed change) are dense fp32 products and run on the matrix cores
-// (v_mfma_f32_32x32x2_f32) with LDS-staged tiles; each one fuses the
-// elementwise step that follows it in the method:
+// summed change) are dense fp32 products and run on the matrix cores, large
+// ones as bf16 plane products (v_mfma_f32_32x32x16_bf16), small ones in fp32
+// (v_mfma_f32_32x32x2_f32); each one fuses the elementwise step that follows it
+// in the method:
 //   forward     A_{l+1} = sigma(A_l W_l + bias)             (section 3)
 //   output      delta_L = (T - Y) Y (1 - Y), error partials  (section 3, fn 5)
 //   backward    delta_l = (delta_{l+1} W_l^T) * A_l (1 - A_l) (section 3)
