@@ -1500,6 +1500,17 @@ double stage_us(int edge, int blocks) {
 
 constexpr int kMinSplitK = 96;   // shortest K range of a split
 
+// Products that are never split (forward, hidden deltas) reach shallow K and
+// part-filled chips, where 128 x 128 tiles take longer to start and gain more
+// from a second block per CU: 16 us, and a stage 0.97 us for one block per CU,
+// 0.8 q - 0.1 for more (measured at K = 150 to 1500, 1500 to 8000 rows;
+// 2958 x 1000 x 400: 41.7 us, 64 x 64 tiles 30.5; 2958 x 2000 x 700: 69.6 and 91.1).
+double unsplit_us(int edge, int blocks, int stages) {
+  const int q = (blocks + kCUs - 1) / kCUs;
+  if (edge == 128) return 16.0 + stages * (q <= 1 ? 0.97 : 0.8 * q - 0.1);
+  return 5.0 + stages * stage_us(edge, blocks);
+}
+
 template <class F>
 Plan plan_product(int M, int N, int K, int max_splits, F&& split_us) {
   Plan best{{64, 64}, 1, K, 1e30};
@@ -1510,7 +1521,8 @@ Plan plan_product(int M, int N, int K, int max_splits, F&& split_us) {
                                                    (size_t)tiles * s * edge * edge <= kMaxSplitFloats));
          ++s) {
       const int per = (stages + s - 1) / s;
-      const double us = 5.0 + per * stage_us(edge, tiles * s) + split_us(s);
+      const double us = max_splits == 1 ? unsplit_us(edge, tiles, per)
+                                        : 5.0 + per * stage_us(edge, tiles * s) + split_us(s);
       if (us < best.us) best = {{edge, edge}, s, per * kStageK, us};
     }
   }
